@@ -109,22 +109,49 @@ __host__ __device__ inline void brick_site(int64_t pl, int M, int& i, int& j, in
   k = bk * 8 + (w & 7);
 }
 
+// Central-difference weights of order 2 ng: first derivative sum_k c_k (f(i+k) - f(i-k)),
+// c = (1/2), (2/3, -1/12), (3/4, -3/20, 1/60); second derivative
+// sum_k a_k (f(i+k) + f(i-k) - 2 f(i)), a = (1), (4/3, -1/12), (3/2, -3/20, 1/90).
+__host__ __device__ inline double first_difference_weight(int ng, int k) {
+  return ng == 1 ? 0.5
+       : ng == 2 ? (k == 1 ? 2.0 / 3.0 : -1.0 / 12.0)
+                 : (k == 1 ? 0.75 : k == 2 ? -0.15 : 1.0 / 60.0);
+}
+__host__ __device__ inline double second_difference_weight(int ng, int k) {
+  return ng == 1 ? 1.0
+       : ng == 2 ? (k == 1 ? 4.0 / 3.0 : -1.0 / 12.0)
+                 : (k == 1 ? 1.5 : k == 2 ? -0.15 : 1.0 / 90.0);
+}
+
 // Eisenstein & Hu (1998) no-wiggle transfer function, k in h/Mpc (Sec. 4: the initial
-// power spectrum uses the Eisenstein-Hu fitting function).
-__host__ __device__ inline double eh_nowiggle_transfer(double k, double Om, double Ob,
-                                                       double h, double Tcmb) {
-  const double theta = Tcmb / 2.7;
+// power spectrum uses the Eisenstein-Hu fitting function).  The part that does not depend on
+// k comes first: three logarithms, a power and a root, which the sigma_8 integral would
+// otherwise take 64 000 times per plan.
+struct EhConstants {
+  double theta, s, ag;
+};
+__host__ __device__ inline EhConstants eh_constants(double Om, double Ob, double h, double Tcmb) {
+  EhConstants c;
+  c.theta = Tcmb / 2.7;
   const double om_m = Om * h * h;
   const double om_b = Ob * h * h;
   const double fb = Ob / Om;
-  const double s = 44.5 * log(9.83 / om_m) / sqrt(1.0 + 10.0 * pow(om_b, 0.75));
-  const double ag = 1.0 - 0.328 * log(431.0 * om_m) * fb + 0.38 * log(22.3 * om_m) * fb * fb;
-  const double ks = 0.43 * k * h * s;
-  const double geff = Om * h * (ag + (1.0 - ag) / (1.0 + ks * ks * ks * ks));
-  const double q = k * theta * theta / geff;
+  c.s = 44.5 * log(9.83 / om_m) / sqrt(1.0 + 10.0 * pow(om_b, 0.75));
+  c.ag = 1.0 - 0.328 * log(431.0 * om_m) * fb + 0.38 * log(22.3 * om_m) * fb * fb;
+  return c;
+}
+__host__ __device__ inline double eh_nowiggle_transfer(double k, const EhConstants& c, double Om,
+                                                       double h) {
+  const double ks = 0.43 * k * h * c.s;
+  const double geff = Om * h * (c.ag + (1.0 - c.ag) / (1.0 + ks * ks * ks * ks));
+  const double q = k * c.theta * c.theta / geff;
   const double L0 = log(2.0 * 2.718281828459045 + 1.8 * q);
   const double C0 = 14.2 + 731.0 / (1.0 + 62.5 * q);
   return L0 / (L0 + C0 * q * q);
+}
+__host__ __device__ inline double eh_nowiggle_transfer(double k, double Om, double Ob,
+                                                       double h, double Tcmb) {
+  return eh_nowiggle_transfer(k, eh_constants(Om, Ob, h, Tcmb), Om, h);
 }
 
 }  // namespace scola

@@ -66,7 +66,7 @@ double Background::E(double a) const {
 // the matter-dominated growing mode (D1 = a, D2 = -3/7 a^2) at a = 1e-6.
 void Background::growth(const std::vector<double>& a_query, std::vector<double>& D1,
                         std::vector<double>& dD1, std::vector<double>& D2,
-                        std::vector<double>& dD2) const {
+                        std::vector<double>& dD2, double a_branch, double* D1_branch) const {
   const size_t n = a_query.size();
   std::vector<size_t> order(n);
   for (size_t i = 0; i < n; ++i) order[i] = i;
@@ -87,28 +87,35 @@ void Background::growth(const std::vector<double>& a_query, std::vector<double>&
   const double a0 = 1e-6;
   double y[4] = {a0, a0 * a0 * a0 * E(a0), -3.0 / 7.0 * a0 * a0,
                  a0 * a0 * a0 * E(a0) * (-6.0 / 7.0 * a0)};
+  // from y at x to xt, in equal steps of at most 1/4096
+  auto advance = [&](double* y, double& x, double xt) {
+    const double hmax = 1.0 / 4096.0;
+    const double span = xt - x;
+    if (!(span > 0.0)) return;
+    const long steps = std::max(1L, (long)std::ceil(span / hmax));
+    const double h = span / steps;
+    for (long s = 0; s < steps; ++s) {
+      double k1[4], k2[4], k3[4], k4[4], t[4];
+      rhs(x, y, k1);
+      for (int c = 0; c < 4; ++c) t[c] = y[c] + 0.5 * h * k1[c];
+      rhs(x + 0.5 * h, t, k2);
+      for (int c = 0; c < 4; ++c) t[c] = y[c] + 0.5 * h * k2[c];
+      rhs(x + 0.5 * h, t, k3);
+      for (int c = 0; c < 4; ++c) t[c] = y[c] + h * k3[c];
+      rhs(x + h, t, k4);
+      for (int c = 0; c < 4; ++c) y[c] += h / 6.0 * (k1[c] + 2 * k2[c] + 2 * k3[c] + k4[c]);
+      x += h;
+    }
+    x = xt;
+  };
   double x = std::log(a0);
-  const double hmax = 1.0 / 4096.0;
   for (size_t qi = 0; qi < n; ++qi) {
     const size_t idx = order[qi];
-    const double xt = std::log(a_query[idx]);
-    const double span = xt - x;
-    if (span > 0.0) {
-      const long steps = std::max(1L, (long)std::ceil(span / hmax));
-      const double h = span / steps;
-      for (long s = 0; s < steps; ++s) {
-        double k1[4], k2[4], k3[4], k4[4], t[4];
-        rhs(x, y, k1);
-        for (int c = 0; c < 4; ++c) t[c] = y[c] + 0.5 * h * k1[c];
-        rhs(x + 0.5 * h, t, k2);
-        for (int c = 0; c < 4; ++c) t[c] = y[c] + 0.5 * h * k2[c];
-        rhs(x + 0.5 * h, t, k3);
-        for (int c = 0; c < 4; ++c) t[c] = y[c] + h * k3[c];
-        rhs(x + h, t, k4);
-        for (int c = 0; c < 4; ++c) y[c] += h / 6.0 * (k1[c] + 2 * k2[c] + 2 * k3[c] + k4[c]);
-        x += h;
-      }
-      x = xt;
+    advance(y, x, std::log(a_query[idx]));
+    if (qi == 0 && D1_branch) {
+      double yb[4] = {y[0], y[1], y[2], y[3]}, xb = x;
+      advance(yb, xb, std::log(a_branch));
+      *D1_branch = yb[0];
     }
     const double a = a_query[idx];
     const double inv = 1.0 / (a * a * a * E(a));
@@ -143,11 +150,12 @@ double Background::beta_standard(double ai, double af) const {
 
 // sigma^2(8 Mpc/h) of k^n_s T(k)^2 with the top-hat window, as an integral over ln k.
 double Background::sigma8_unnormalised() const {
+  const EhConstants c = eh_constants(Om, Ob, h, Tcmb);
   auto f = [&](double lnk) {
     const double k = std::exp(lnk);
     const double x = 8.0 * k;
     const double W = 3.0 * (std::sin(x) - x * std::cos(x)) / (x * x * x);
-    const double T = eh_nowiggle_transfer(k, Om, Ob, h, Tcmb);
+    const double T = eh_nowiggle_transfer(k, c, Om, h);
     return k * k * k * std::pow(k, ns) * T * T * W * W / (2.0 * M_PI * M_PI);
   };
   return integrate(f, std::log(1e-6), std::log(1e3), 8000, 8);

@@ -19,13 +19,24 @@ struct BlockMap {
   int xcd_remap = 1;       // spread consecutive logical blocks over one XCD (see kernels)
 };
 
+// Per-plan tables of the periodic solves on an N^3 grid (kernels_fft.hip): exp(-2 pi i m / N),
+// the FDA Laplacian's symbol per axis, and the initial spectrum's amplitude over |m|^2.
+struct PeriodicTables {
+  const double2* tw = nullptr;
+  const double* symbol = nullptr;
+  const double* spectrum = nullptr;
+  int N = 0;
+};
+// |m|^2 of a mode is at most 3 (N / 2)^2
+inline size_t spectrum_entries(int N) { return 3 * (size_t)(N / 2) * (size_t)(N / 2) + 1; }
+size_t periodic_table_bytes(int N);
 struct SetupArgs {
   const double* white_noise;
-  double2* cbuf;
+  double2* cbuf;            // N^3 complex scratch
   double* phi1;
   double* phi2;
-  int N;
-  double L, amplitude, ns, Om, Ob, h, Tcmb, growth2;
+  PeriodicTables tables;
+  double L, amplitude, ns, Om, Ob, h, Tcmb, growth2;   // the initial spectrum
   int ng = 1;               // finite differences of order 2 ng
 };
 
@@ -151,7 +162,14 @@ struct AdjointArgs {
 
 enum ParticleMode { kDepositOnly = 0, kStep = 1, kStepNoDeposit = 2, kFinalKick = 3, kInit = 4 };
 
+// Fills the tables of an N^3 grid in buf (periodic_table_bytes(N) bytes, 16-byte aligned) for
+// the spectrum and order of `a`.
+hipError_t launch_periodic_tables(void* buf, int N, const SetupArgs& a, PeriodicTables* out,
+                                  hipStream_t s);
+// white noise -> phi1, phi2 (A.1, A.2); the radix-2 form (order 2) keeps the rounding that
+// gradients of FP32 plans depend on (kernels_setup_radix2.hip)
 hipError_t launch_setup_potentials(const SetupArgs& a, hipStream_t s);
+hipError_t launch_setup_potentials_radix2(const SetupArgs& a, hipStream_t s);
 template <typename T>
 hipError_t launch_setup_boxes(const BoxSetupArgs& a, T* xres, T* pres, hipStream_t s);
 
@@ -188,17 +206,15 @@ template <typename T>
 hipError_t launch_adj_setup_scatter(const BoxSetupArgs& b, const T* lam_psi1,
                                     const T* lam_psi2, double* lam_psig,
                                     const double* lam_bc0, double* lam_phi1, hipStream_t s);
-hipError_t launch_adj_phi_from_psi(const double* lam_psig, double* lam_phi1, double2* cbuf,
-                                   int N, hipStream_t s);
+// Transposes of Psi = D phi and of the second-order Poisson equation: lam_phi1 += D^T lam_Psi1,
+// lam_s = Delta^-1 D^T lam_Psi2 (lam_psig: the six fields); and of the initial-condition
+// filter: grad_w from lam_phi1.
+hipError_t launch_adj_phi_from_psi(const SetupArgs& a, const double* lam_psig, double* lam_phi1,
+                                   double* lam_s, hipStream_t s);
+hipError_t launch_adj_white_noise(const SetupArgs& a, const double* lam_phi1, double* grad_w,
+                                  hipStream_t s);
 hipError_t launch_adj_source(const double* phi1, const double* lam_s, double* f6,
                              double* lam_phi1, int N, hipStream_t s);
-hipError_t launch_real_to_complex(const double* in, double2* out, int64_t n, hipStream_t s);
-// FP64 set-up pieces reused by the adjoint
-hipError_t fft3d_forward(double2* c, int N, hipStream_t s);
-hipError_t fft3d_inverse(double2* c, int N, hipStream_t s);
-hipError_t launch_ic_filter(const SetupArgs& a, hipStream_t s);
-hipError_t launch_inverse_laplacian(double2* c, int N, int ng, hipStream_t s);
-hipError_t launch_take_real(const double2* c, double* out, double scale, int64_t n, hipStream_t s);
 
 // Monolithic periodic tCOLA of the full box (N^3 particles in lattice order, [3][N^3]
 // component arrays, a periodic N^3 node grid).
@@ -220,10 +236,11 @@ hipError_t launch_tcola_setup(const TcolaArgs<T>& a, const double* phi1, const d
                               hipStream_t s);
 template <typename T>
 hipError_t launch_tcola_particles(const TcolaArgs<T>& a, int mode, hipStream_t s);
-// rec_delta / rec_phi: optional N^3 arrays receiving this solve's delta and potential
+// mass mesh -> delta -> potential (the mass mesh is cleared); rec_delta / rec_phi: optional
+// N^3 arrays receiving this solve's delta and potential
 template <typename T>
-hipError_t launch_tcola_poisson(const TcolaArgs<T>& a, double2* cbuf, T* phi, T* rec_delta,
-                                T* rec_phi, hipStream_t s);
+hipError_t launch_tcola_poisson(const TcolaArgs<T>& a, const PeriodicTables& t, double2* cbuf,
+                                T* phi, T* rec_delta, T* rec_phi, hipStream_t s);
 template <typename T>
 hipError_t launch_tcola_output(const TcolaArgs<T>& a, T* pos, T* mom, unsigned long long* grid,
                                T* density, int N_out, double cell, double L, hipStream_t s);

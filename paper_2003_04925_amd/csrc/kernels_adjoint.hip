@@ -539,26 +539,6 @@ __global__ void k_adj_boundary(const TileDesc* __restrict__ tiles, int n_tiles,
   }
 }
 
-// Transpose of Psi = D phi (central difference, periodic): D^T f (q) = (f(q-e) - f(q+e)) / 2.
-// lam_phi1 += D^T lam_Psi1_global; the second-order part D^T lam_Psi2_global goes to the
-// complex FFT buffer.
-__global__ void k_adj_phi_from_psi(const double* __restrict__ g, double* __restrict__ lam_phi1,
-                                   double2* __restrict__ cbuf, int N) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t N3 = (int64_t)N * N * N;
-  if (i >= N3) return;
-  const int x = (int)(i / ((int64_t)N * N)), y = (int)((i / N) % N), z = (int)(i % N);
-  auto at = [&](int c, int dx, int dy, int dz) {
-    return g[c * N3 + ((int64_t)wrapn(x + dx, N) * N + wrapn(y + dy, N)) * N + wrapn(z + dz, N)];
-  };
-  double a1 = 0.5 * (at(0, -1, 0, 0) - at(0, 1, 0, 0) + at(1, 0, -1, 0) - at(1, 0, 1, 0) +
-                     at(2, 0, 0, -1) - at(2, 0, 0, 1));
-  double a2 = 0.5 * (at(3, -1, 0, 0) - at(3, 1, 0, 0) + at(4, 0, -1, 0) - at(4, 0, 1, 0) +
-                     at(5, 0, 0, -1) - at(5, 0, 0, 1));
-  lam_phi1[i] += a1;
-  cbuf[i] = make_double2(a2, 0.0);
-}
-
 // Fields of the second-order source transpose: with S = sum_{i>j} [phi_,ii phi_,jj -
 // phi_,ij^2], dS/dphi^T lam_S = sum_i D_iD_i (lam_S sum_{j != i} phi_,jj)
 //                             - 2 sum_{i>j} D_iD_j (lam_S phi_,ij).
@@ -615,12 +595,6 @@ __global__ void k_adj_source_apply(const double* __restrict__ f6, double* __rest
                  2.0 * (dm(3, 0, 1) + dm(4, 0, 2) + dm(5, 1, 2));
 }
 
-__global__ void k_real_to_complex_adj(const double* __restrict__ in, double2* __restrict__ out,
-                                      int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = make_double2(in[i], 0.0);
-}
-
 }  // namespace
 
 template <typename T>
@@ -658,26 +632,12 @@ hipError_t launch_adj_setup_scatter(const BoxSetupArgs& b, const T* lam_psi1,
   return hipGetLastError();
 }
 
-hipError_t launch_adj_phi_from_psi(const double* lam_psig, double* lam_phi1, double2* cbuf,
-                                   int N, hipStream_t s) {
-  const int64_t n3 = (int64_t)N * N * N;
-  hipLaunchKernelGGL(k_adj_phi_from_psi, dim3((unsigned)((n3 + kBlock - 1) / kBlock)),
-                     dim3(kBlock), 0, s, lam_psig, lam_phi1, cbuf, N);
-  return hipGetLastError();
-}
-
 hipError_t launch_adj_source(const double* phi1, const double* lam_s, double* f6,
                              double* lam_phi1, int N, hipStream_t s) {
   const int64_t n3 = (int64_t)N * N * N;
   const unsigned g = (unsigned)((n3 + kBlock - 1) / kBlock);
   hipLaunchKernelGGL(k_adj_source_fields, dim3(g), dim3(kBlock), 0, s, phi1, lam_s, f6, N);
   hipLaunchKernelGGL(k_adj_source_apply, dim3(g), dim3(kBlock), 0, s, f6, lam_phi1, N);
-  return hipGetLastError();
-}
-
-hipError_t launch_real_to_complex(const double* in, double2* out, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_real_to_complex_adj, dim3((unsigned)((n + kBlock - 1) / kBlock)),
-                     dim3(kBlock), 0, s, in, out, n);
   return hipGetLastError();
 }
 

@@ -11,8 +11,8 @@
 // removed), the central-difference gradient of the same order and CiC interpolation, then
 // the same COLA kick and drift.  Particles are in lattice order; every
 // position is formed in FP64 as in the box kernels; deposits are 64-bit fixed point (2^40
-// units per particle), exact and order independent.  The Poisson solve reuses the FP64
-// FFTs of the set-up (a reference path: its cost is not part of the sCOLA step).
+// units per particle), exact and order independent.  The Poisson solve is the FP64 periodic
+// one of kernels_fft.hip.
 #include <type_traits>
 
 #include "common.h"
@@ -22,14 +22,6 @@
 namespace scola {
 
 namespace {
-
-// Central first-difference weights of order 2 ng: (1/2), (2/3, -1/12), (3/4, -3/20, 1/60).
-__device__ inline double tc_grad_weight(int ng, int k) {
-  return ng == 1 ? 0.5
-       : ng == 2 ? (k == 1 ? 2.0 / 3.0 : -1.0 / 12.0)
-                 : (k == 1 ? 0.75 : k == 2 ? -0.15 : 1.0 / 60.0);
-}
-
 
 __device__ __forceinline__ int pwrap(int i, int N) { return i & (N - 1); }   // N: power of 2
 
@@ -50,7 +42,7 @@ __global__ void __launch_bounds__(kBlock) k_tcola_setup(TcolaArgs<T> a, const do
   T* s2 = const_cast<T*>(a.psi2);
   double g1[3] = {0.0, 0.0, 0.0}, g2[3] = {0.0, 0.0, 0.0};
   for (int k = 1; k <= a.ng; ++k) {
-    const double c = tc_grad_weight(a.ng, k);
+    const double c = first_difference_weight(a.ng, k);
     g1[0] += c * (at(phi1, x + k, y, z) - at(phi1, x - k, y, z));
     g1[1] += c * (at(phi1, x, y + k, z) - at(phi1, x, y - k, z));
     g1[2] += c * (at(phi1, x, y, z + k) - at(phi1, x, y, z - k));
@@ -127,7 +119,7 @@ __global__ void __launch_bounds__(kBlock) k_tcola_particles(TcolaArgs<T> a) {
             // central difference of order 2 ng
             T sx = 0, sy = 0, sz = 0;
             for (int o = 1; o <= a.ng; ++o) {
-              const T c = (T)tc_grad_weight(a.ng, o);
+              const T c = (T)first_difference_weight(a.ng, o);
               sx += c * (ph(i + o, j, k) - ph(i - o, j, k));
               sy += c * (ph(i, j + o, k) - ph(i, j - o, k));
               sz += c * (ph(i, j, k + o) - ph(i, j, k - o));
@@ -176,29 +168,6 @@ __global__ void __launch_bounds__(kBlock) k_tcola_particles(TcolaArgs<T> a) {
       atomicAdd(a.rho + ((int64_t)pwrap(j0[0] + ((c >> 2) & 1), N) * N +
                          pwrap(j0[1] + ((c >> 1) & 1), N)) * N + pwrap(j0[2] + (c & 1), N),
                 (unsigned long long)w[c]);
-}
-
-// delta = mass - 1 (one particle per cell) as complex FFT input; the mass mesh is cleared
-// for the next deposit, and delta optionally recorded.
-template <typename T>
-__global__ void k_tcola_density(unsigned long long* __restrict__ rho, double2* __restrict__ c,
-                                T* __restrict__ record, int64_t n3) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n3) return;
-  const double d = (double)(long long)rho[i] * kFixedInv - 1.0;
-  rho[i] = 0ull;
-  c[i] = make_double2(d, 0.0);
-  if (record) record[i] = (T)d;
-}
-
-template <typename T>
-__global__ void k_tcola_potential(const double2* __restrict__ c, T* __restrict__ phi,
-                                  T* __restrict__ record, int64_t n3) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n3) return;
-  const T v = (T)(c[i].x / (double)n3);
-  phi[i] = v;
-  if (record) record[i] = v;
 }
 
 // Final positions (Mpc/h in [0, L)) and momenta at the lattice index, and the periodic CiC of
@@ -286,24 +255,6 @@ hipError_t launch_tcola_particles(const TcolaArgs<T>& a, int mode, hipStream_t s
   return hipGetLastError();
 }
 
-// The FDA Poisson solve of the periodic box: mass mesh -> delta -> potential (FP64 FFTs).
-template <typename T>
-hipError_t launch_tcola_poisson(const TcolaArgs<T>& a, double2* cbuf, T* phi, T* rec_delta,
-                                T* rec_phi, hipStream_t s) {
-  const int N = a.N;
-  const int64_t n3 = (int64_t)N * N * N;
-  hipLaunchKernelGGL(k_tcola_density<T>, dim3(blocks_of(n3)), dim3(kBlock), 0, s, a.rho, cbuf,
-                     rec_delta, n3);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if ((e = fft3d_forward(cbuf, N, s)) != hipSuccess) return e;
-  if ((e = launch_inverse_laplacian(cbuf, N, a.ng, s)) != hipSuccess) return e;
-  if ((e = fft3d_inverse(cbuf, N, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_tcola_potential<T>, dim3(blocks_of(n3)), dim3(kBlock), 0, s, cbuf, phi,
-                     rec_phi, n3);
-  return hipGetLastError();
-}
-
 template <typename T>
 hipError_t launch_tcola_output(const TcolaArgs<T>& a, T* pos, T* mom, unsigned long long* grid,
                                T* density, int N_out, double cell, double L, hipStream_t s) {
@@ -327,8 +278,6 @@ hipError_t launch_tcola_output(const TcolaArgs<T>& a, T* pos, T* mom, unsigned l
   template hipError_t launch_tcola_setup<T>(const TcolaArgs<T>&, const double*,             \
                                             const double*, hipStream_t);                    \
   template hipError_t launch_tcola_particles<T>(const TcolaArgs<T>&, int, hipStream_t);     \
-  template hipError_t launch_tcola_poisson<T>(const TcolaArgs<T>&, double2*, T*, T*, T*,    \
-                                              hipStream_t);                                 \
   template hipError_t launch_tcola_output<T>(const TcolaArgs<T>&, T*, T*, unsigned long long*, \
                                              T*, int, double, double, hipStream_t);
 SCOLA_TCOLA_INSTANTIATE(float)

@@ -91,12 +91,17 @@ struct scola_plan {
   int64_t P = 0, G = 0, H = 0;
   std::vector<double> table;          // (n_steps + 1) x 8 scalar rows of cfg.a_f
   std::vector<double> D1, D2;         // growth at t_0 .. t_n of cfg.a_f
-  double growth2 = 1.0;               // (D1(a_i) / D1(1))^2
+  // (D1(a_i) / D1(1))^2, integrated once per plan (57 000 Runge-Kutta steps: on every set-up
+  // they cost 1.2 ms of host time, against 0.38 ms of the GPU's on a whole run of 32^3
+  // particles)
+  double growth2 = 1.0;
   std::vector<TimeClass> tclasses;    // [0]: cfg.a_f; then every other tile final time
   scola_layout lay{};
   TileDesc* d_tiles = nullptr;
   void* d_twiddles = nullptr;
   void* d_eigen = nullptr;
+  void* d_periodic = nullptr;  // tables of the periodic FP64 solves
+  PeriodicTables periodic;
   void* d_sine = nullptr;      // FP32 plans: split sine matrices of the matrix-core DST
   Maps part, p1, p2, p3;
   // launch schedule per size class (index as part.class_M), chosen by scola_plan_tune
@@ -339,8 +344,6 @@ void upload_tables(scola_plan* p) {
             "hipMemcpy(eigen)");
 }
 
-// growth2: when given, (D1(a_i) / D1(1))^2 from the same integration, which scales
-// P_lin(k, 1) to the initial time (Sec. 3.1, A.1).
 void compute_step_table(const scola_config& c, const Background& bg, std::vector<double>& table,
                         std::vector<double>& D1out, std::vector<double>& D2out,
                         double* growth2 = nullptr);
@@ -349,6 +352,7 @@ void build_step_table(scola_plan* p) {
   compute_step_table(p->cfg, p->bg, p->table, p->D1, p->D2, &p->growth2);
 }
 
+// growth2: when given, (D1(a_i) / D1(1))^2, with which P_lin(k, a_i) = growth2 P_lin(k, 1).
 void compute_step_table(const scola_config& c, const Background& bg, std::vector<double>& table,
                         std::vector<double>& D1out, std::vector<double>& D2out,
                         double* growth2) {
@@ -358,11 +362,18 @@ void compute_step_table(const scola_config& c, const Background& bg, std::vector
   for (int k = 0; k < n; ++k) half[k] = 0.5 * (t[k] + t[k + 1]);
   std::vector<double> q(t);
   q.push_back(c.a_i);
-  if (growth2) q.push_back(1.0);
   std::vector<double> D1, dD1, D2, dD2;
-  bg.growth(q, D1, dD1, D2, dD2);
+  double today = 0.0;                               // D1(1), on a branch of the integration
+  const bool branch = growth2 && c.a_i <= 1.0;
+  bg.growth(q, D1, dD1, D2, dD2, 1.0, branch ? &today : nullptr);
   const double n1 = D1[n + 1];                      // D1 normalised to 1 at a_i
-  if (growth2) *growth2 = (n1 / D1[n + 2]) * (n1 / D1[n + 2]);
+  if (growth2 && !branch) {                         // the run starts after a = 1
+    std::vector<double> d, dd, e, ee;
+    bg.growth({1.0, c.a_i}, d, dd, e, ee);
+    *growth2 = (d[1] / d[0]) * (d[1] / d[0]);
+  } else if (growth2) {
+    *growth2 = (n1 / today) * (n1 / today);
+  }
   D1out.assign(n + 1, 0.0);
   D2out.assign(n + 1, 0.0);
   for (int k = 0; k <= n; ++k) {
@@ -782,13 +793,9 @@ struct Runner {
   }
 };
 
-SetupArgs setup_args(scola_plan* p, const double* w, void* ws) {
-  SetupArgs a;
-  a.white_noise = w;
-  a.cbuf = reinterpret_cast<double2*>(ws_ptr(ws, p->lay.cbuf));
-  a.phi1 = reinterpret_cast<double*>(ws_ptr(ws, p->lay.phi1));
-  a.phi2 = reinterpret_cast<double*>(ws_ptr(ws, p->lay.phi2));
-  a.N = p->N_lpt;
+// The initial spectrum and finite-difference order of the plan.
+SetupArgs spectrum_args(const scola_plan* p) {
+  SetupArgs a{};
   a.L = p->cfg.L;
   a.amplitude = p->bg.amplitude;
   a.ns = p->bg.ns;
@@ -796,11 +803,18 @@ SetupArgs setup_args(scola_plan* p, const double* w, void* ws) {
   a.Ob = p->bg.Ob;
   a.h = p->bg.h;
   a.Tcmb = p->bg.Tcmb;
-  // P_lin(k, a_i) = P_lin(k, 1) (D1(a_i) / D1(1))^2, from the plan's one growth integration
-  // (57 000 Runge-Kutta steps: on every set-up they cost more than the GPU's work on 32^3
-  // particles, 1.2 ms of host time against 0.38 ms)
   a.growth2 = p->growth2;
   a.ng = p->ng;
+  return a;
+}
+
+SetupArgs setup_args(scola_plan* p, const double* w, void* ws) {
+  SetupArgs a = spectrum_args(p);
+  a.white_noise = w;
+  a.cbuf = reinterpret_cast<double2*>(ws_ptr(ws, p->lay.cbuf));
+  a.phi1 = reinterpret_cast<double*>(ws_ptr(ws, p->lay.phi1));
+  a.phi2 = reinterpret_cast<double*>(ws_ptr(ws, p->lay.phi2));
+  a.tables = p->periodic;
   return a;
 }
 
@@ -826,7 +840,12 @@ BoxSetupArgs box_setup_args(scola_plan* p, void* ws) {
 template <typename T>
 void do_setup(scola_plan* p, const double* w, void* ws, hipStream_t s) {
   SetupArgs a = setup_args(p, w, ws);
-  hip_check(launch_setup_potentials(a, s), "set-up potentials");
+  // where scola_backward can follow in FP32, the rounding of phi decides which side of a cell
+  // face a few particles take (see launch_setup_potentials_radix2)
+  const bool fp32_reverse = std::is_same<T, float>::value && p->cfg.checkpoint_every > 0 &&
+                            p->ng == 1 && p->N_lpt == p->cfg.Np && p->tclasses.size() == 1;
+  hip_check(fp32_reverse ? launch_setup_potentials_radix2(a, s) : launch_setup_potentials(a, s),
+            "set-up potentials");
   BoxSetupArgs b = box_setup_args(p, ws);
   hip_check(launch_setup_boxes<T>(b, reinterpret_cast<T*>(ws_ptr(ws, p->lay.x_res)),
                                   reinterpret_cast<T*>(ws_ptr(ws, p->lay.p_res)), s),
@@ -1193,24 +1212,14 @@ void do_backward(scola_plan* p, const T* lam_dens, double* grad_w, void* ws, hip
   double* lam_phi1 = g + 6 * N3;      // N^3
   double* lam_s = g + 7 * N3;         // N^3
   double* f6 = g + 8 * N3;            // 6 N^3
-  double2* cbuf = reinterpret_cast<double2*>(ws_ptr(ws, l.cbuf));
   zero_bytes(g, 7 * (size_t)N3 * 8, s);
   BoxSetupArgs b = box_setup_args(p, ws);
   hip_check(launch_adj_setup_scatter<T>(b, a.lam_psi1, a.lam_psi2, lam_psig, a.lam_bc0, lam_phi1, s),
             "adjoint set-up scatter");
-  hip_check(launch_adj_phi_from_psi(lam_psig, lam_phi1, cbuf, N, s), "adjoint D^T");
-  hip_check(fft3d_forward(cbuf, N, s), "fft");
-  hip_check(launch_inverse_laplacian(cbuf, N, p->ng, s), "adjoint Poisson (2LPT)");
-  hip_check(fft3d_inverse(cbuf, N, s), "fft");
-  hip_check(launch_take_real(cbuf, lam_s, 1.0 / (double)N3, N3, s), "take real");
-  hip_check(launch_adj_source(reinterpret_cast<const double*>(ws_ptr(ws, l.phi1)), lam_s, f6,
-                              lam_phi1, N, s), "adjoint second-order source");
-  hip_check(launch_real_to_complex(lam_phi1, cbuf, N3, s), "real to complex");
-  hip_check(fft3d_forward(cbuf, N, s), "fft");
   SetupArgs sa = setup_args(p, nullptr, ws);
-  hip_check(launch_ic_filter(sa, s), "adjoint IC filter");
-  hip_check(fft3d_inverse(cbuf, N, s), "fft");
-  hip_check(launch_take_real(cbuf, grad_w, 1.0 / (double)N3, N3, s), "take real");
+  hip_check(launch_adj_phi_from_psi(sa, lam_psig, lam_phi1, lam_s, s), "adjoint D^T (2LPT)");
+  hip_check(launch_adj_source(sa.phi1, lam_s, f6, lam_phi1, N, s), "adjoint second-order source");
+  hip_check(launch_adj_white_noise(sa, lam_phi1, grad_w, s), "adjoint IC filter");
 }
 
 void drop_graph(scola_plan* p) {
@@ -1416,7 +1425,7 @@ void do_tcola(scola_plan* p, const double* w, void* pos, void* mom, void* dens, 
   auto poisson = [&]() {
     T* rd = rec_d ? reinterpret_cast<T*>(rec_d) + (size_t)force * N3 : nullptr;
     T* rp = rec_p ? reinterpret_cast<T*>(rec_p) + (size_t)force * N3 : nullptr;
-    hip_check(launch_tcola_poisson<T>(a, sa.cbuf, phi, rd, rp, s), "tCOLA Poisson");
+    hip_check(launch_tcola_poisson<T>(a, sa.tables, sa.cbuf, phi, rd, rp, s), "tCOLA Poisson");
     ++force;
   };
   a.sc = StepScalars{};
@@ -1611,6 +1620,12 @@ scola_status scola_plan_create(const scola_config* cfg, const scola_cosmology* c
     // the interior x planes, then the 2 (ng + 1) shell planes
     const int ng = p->ng;
     build_maps(p->p3, p->desc, [ng](const TileDesc& d) { return d.M - 1 + 2 * (ng + 1); });
+    hip_check(hipMalloc(&p->d_periodic, periodic_table_bytes(p->N_lpt)), "hipMalloc(periodic)");
+    // on the device (one entry per |m|^2 of the LPT grid); the host waits for it, as for the
+    // copies below, so that every stream may use the plan
+    hip_check(launch_periodic_tables(p->d_periodic, p->N_lpt, spectrum_args(p),
+                                     &p->periodic, nullptr), "periodic tables");
+    hip_check(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
     upload_maps(p->part);
     upload_maps(p->p1);
     upload_maps(p->p2);
@@ -1642,6 +1657,7 @@ scola_status scola_plan_destroy(scola_plan* p) {
   if (p->d_barrier) hipFree(p->d_barrier);
   if (p->d_twiddles) hipFree(p->d_twiddles);
   if (p->d_eigen) hipFree(p->d_eigen);
+  if (p->d_periodic) hipFree(p->d_periodic);
   if (p->d_sine) hipFree(p->d_sine);
   delete p;
   return SCOLA_OK;
