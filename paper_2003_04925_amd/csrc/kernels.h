@@ -55,6 +55,7 @@ struct BoxSetupArgs {
   int64_t P;
   int ng = 1;               // finite differences of order 2 ng; Phi_BC^0 on [-ng, M+ng]^3
   int Np = 0;               // lattice particles per side (a multiple of N)
+  int max_M = 0;            // largest box side
 };
 
 template <typename T>

@@ -834,6 +834,7 @@ BoxSetupArgs box_setup_args(scola_plan* p, void* ws) {
   b.P = p->P;
   b.ng = p->ng;
   b.Np = p->cfg.Np;
+  b.max_M = p->max_M;
   return b;
 }
 
