@@ -36,9 +36,15 @@ k_particles(ParticleArgs<T> a, BlockMap m) {
   if (L < m.count) particles_block<T, MODE>(a, m, L);
 }
 
-// The force-evaluating modes at gradient order 2 NG, NG = 2 or 3 (Sec. 3).
+// The force-evaluating modes at gradient order 2 NG, NG = 2 or 3 (Sec. 3).  FP32: held to 6
+// waves per SIMD (80 registers) at order 4 and 5 (96) at order 6, without spills.
+template <typename T, int NG>
+constexpr int wide_waves() {
+  return std::is_same<T, float>::value ? (NG == 2 ? 6 : 5) : 1;
+}
 template <typename T, int MODE, int NG>
-__global__ void __launch_bounds__(kBlock) k_particles_wide(ParticleArgs<T> a, BlockMap m) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(wide_waves<T, NG>())))
+k_particles_wide(ParticleArgs<T> a, BlockMap m) {
   const int L = logical_block(m);
   if (L < m.count) particles_block<T, MODE, NG>(a, m, L);
 }

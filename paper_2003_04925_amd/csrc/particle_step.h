@@ -427,7 +427,7 @@ __device__ __forceinline__ constexpr double grad_weight(int k) {
 // CiC corner c in [0, M] (others carry zero weight) the component along axis a is
 // sum_k c_k (Phi(c + k e_a) - Phi(c - k e_a)); `at(kx, ky, kz)` returns the potential at
 // node j0 - NG + k (k in 0..2 NG + 1 per axis; a finite stand-in where only zero weights
-// use it).
+// use it).  The two corners of a line along an axis share its 2 NG + 2 nodes.
 template <typename T, int NG, typename At>
 __device__ __forceinline__ void gather_force_wide(int M, const int (&j0)[3], const T (&fr)[3],
                                                   At at, T (&g)[3]) {
@@ -437,37 +437,95 @@ __device__ __forceinline__ void gather_force_wide(int M, const int (&j0)[3], con
     w[a][0] = j0[a] >= 0 ? T(1) - fr[a] : T(0);
     w[a][1] = j0[a] + 1 <= M ? fr[a] : T(0);
   }
-  T gx = 0, gy = 0, gz = 0;
+  // the four lines along each axis in a rolled loop: unrolled, their nodes would be shared
+  // between the axes (56 reads instead of 72), but the registers for it spill
+  T sum[3] = {T(0), T(0), T(0)};
 #pragma unroll 1
-  for (int c = 0; c < 8; ++c) {
-    const int dx = (c >> 2) & 1, dy = (c >> 1) & 1, dz = c & 1;
-    const T wc = w[0][dx] * w[1][dy] * w[2][dz];
-    const int X = NG + dx, Y = NG + dy, Z = NG + dz;
-    T sx = 0, sy = 0, sz = 0;
+  for (int pq = 0; pq < 4; ++pq) {
+    const int p = pq >> 1, q = pq & 1;
 #pragma unroll
-    for (int k = 1; k <= NG; ++k) {
-      const T ck = (T)grad_weight<NG>(k);
-      sx += ck * (at(X + k, Y, Z) - at(X - k, Y, Z));
-      sy += ck * (at(X, Y + k, Z) - at(X, Y - k, Z));
-      sz += ck * (at(X, Y, Z + k) - at(X, Y, Z - k));
+    for (int a = 0; a < 3; ++a) {
+      // the line along axis a through corner p, q of the other two axes
+      T n[2 * NG + 2];
+#pragma unroll
+      for (int k = 0; k < 2 * NG + 2; ++k)
+        n[k] = a == 0 ? at(k, NG + p, NG + q) : a == 1 ? at(NG + p, k, NG + q)
+                                                       : at(NG + p, NG + q, k);
+      T d0 = 0, d1 = 0;
+#pragma unroll
+      for (int k = 1; k <= NG; ++k) {
+        d0 += (T)grad_weight<NG>(k) * (n[NG + k] - n[NG - k]);
+        d1 += (T)grad_weight<NG>(k) * (n[NG + 1 + k] - n[NG + 1 - k]);
+      }
+      const T wp = a == 0 ? (p ? w[1][1] : w[1][0]) : (p ? w[0][1] : w[0][0]);
+      const T wq = a == 2 ? (q ? w[1][1] : w[1][0]) : (q ? w[2][1] : w[2][0]);
+      sum[a] += wp * wq * (w[a][0] * d0 + w[a][1] * d1);
     }
-    gx += wc * sx;
-    gy += wc * sy;
-    gz += wc * sz;
   }
-  g[0] = gx;
-  g[1] = gy;
-  g[2] = gz;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) g[a] = sum[a];
+}
+
+// The LDS window of a block's stencils at gradient order 2 NG: nodes [lo - NG, hi + 1 + NG]
+// per axis of the cell extent, laid out x by x with runtime pitches.
+template <int NG>
+struct WideWindow {
+  int o[3], w[3], wyz;
+  bool fits;
+  __device__ explicit WideWindow(const CellRange& cr) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      o[a] = cr.lo[a] - NG;
+      w[a] = cr.hi[a] - cr.lo[a] + 2 + 2 * NG;
+    }
+    wyz = w[1] * w[2];
+    fits = cr.any && w[0] <= kWindow && wyz <= kWindow && w[0] * wyz <= kWindow;
+  }
+};
+
+// stage_window_direct for the window of order 2 NG (NG > 1; FP32 plans): coordinates clamped
+// into the padded grid [-NG, M + NG], which changes only reads that carry zero weight.
+template <typename T, int NG>
+__device__ __forceinline__ bool stage_wide_direct(const T* __restrict__ phi, int M,
+                                                  const CellRange& cr, T* win) {
+  if constexpr (sizeof(T) != 4) {
+    return false;
+  } else {
+    const WideWindow<NG> v(cr);
+    if (!v.fits) return false;
+    const int Mp = M + 1 + 2 * NG, Mp2 = Mp * Mp;
+    const __amdgpu_buffer_rsrc_t rs = buffer_of(phi, (unsigned)(Mp2 * Mp * (int)sizeof(T)));
+    const float inv = 1.0f / (float)v.w[2];
+    for (int p0 = 0; p0 < v.wyz; p0 += kBlock) {
+      const int pos = p0 + (int)threadIdx.x;
+      if (pos < v.wyz) {
+        const int y = (int)(((float)pos + 0.5f) * inv), z = pos - y * v.w[2];
+        const int ny = min(max(v.o[1] + y, -NG), M + NG), nz = min(max(v.o[2] + z, -NG), M + NG);
+        const unsigned gcol = (unsigned)(((ny + NG) * Mp + nz + NG) * (int)sizeof(T));
+        T* const wave_base = win + __builtin_amdgcn_readfirstlane(pos & ~63);
+        for (int x = 0; x < v.w[0]; ++x) {
+          const int nx = min(max(v.o[0] + x, -NG), M + NG);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              rs, (__attribute__((address_space(3))) void*)(wave_base + x * v.wyz), 4, gcol,
+              (nx + NG) * Mp2 * (int)sizeof(T), 0, 0);
+        }
+      }
+    }
+    return true;
+  }
 }
 
 // Force at u for the 256 particles of a block at gradient order 2 NG (NG > 1) on the padded
-// potential [-NG, M + NG]^3: the block's stencil nodes [min j0 - NG, max j0 + 1 + NG] are
-// staged in an LDS window sized to that extent when it fits, else gathered from global
-// memory; coordinates are clamped into the padded grid, which changes only reads that
-// carry zero weight.  Must be called by all threads of the block.
+// potential [-NG, M + NG]^3, with the kept extent as in block_force: the block's stencil nodes
+// in an LDS window sized to the extent when it holds at most kWindow, else from global
+// memory.  Must be called by all threads of the block.  (Order 4 on the 64 boxes of 64^3:
+// 0.51 ms a step with the window staged after the extent's reduction, node by node through
+// registers, and 96 reads per particle in a rolled loop; 0.42 with the kept extent, direct
+// staging and the lines' nodes shared.)
 template <typename T, int NG>
 __device__ __forceinline__ void block_force_wide(const T* __restrict__ phi, int M, double ux,
                                                  double uy, double uz, T* win, int* bounds,
+                                                 bool hinted, const CellRange& hc, bool staged,
                                                  T (&g)[3]) {
   g[0] = g[1] = g[2] = T(0);
   const double hiu = (double)M + 1.0;
@@ -485,29 +543,41 @@ __device__ __forceinline__ void block_force_wide(const T* __restrict__ phi, int 
   }
   const int Mp = M + 1 + 2 * NG;
   auto cl = [&](int v) { return min(max(v, -NG), M + NG) + NG; };   // padded index
-  const CellRange cr = block_cells(in, j0, bounds);
+  CellRange cr = hc;
+  bool held = false;
+  if (hinted) {
+    hint_to_slots(in, j0, cr, bounds);
+    // this wave's direct-to-LDS loads must have landed before the barrier (see block_force)
+    if (staged) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    held = hint_holds(bounds);
+  }
+  if (!held) cr = block_cells(in, j0, bounds);
   if (cr.any) {
-    const int ox = cr.lo[0] - NG, oy = cr.lo[1] - NG, oz = cr.lo[2] - NG;
-    const int wx = cr.hi[0] - cr.lo[0] + 2 + 2 * NG, wy = cr.hi[1] - cr.lo[1] + 2 + 2 * NG,
-              wz = cr.hi[2] - cr.lo[2] + 2 + 2 * NG;
-    const int wyz = wy * wz;
-    if (wx * wyz <= kWindow) {
-      for (int pos = threadIdx.x; pos < wyz; pos += blockDim.x) {
-        const int ey = pos / wz, ez = pos - ey * wz;
-        const int64_t col = (int64_t)cl(oy + ey) * Mp + cl(oz + ez);
-        for (int x = 0; x < wx; ++x) win[x * wyz + pos] = phi[(int64_t)cl(ox + x) * Mp * Mp + col];
+    const WideWindow<NG> v(cr);
+    if (v.fits) {
+      if (!(held && staged)) {
+        const float inv = 1.0f / (float)v.w[2];
+        for (int pos = threadIdx.x; pos < v.wyz; pos += kBlock) {
+          const int y = (int)(((float)pos + 0.5f) * inv), z = pos - y * v.w[2];
+          const T* const col = phi + (cl(v.o[1] + y) * Mp + cl(v.o[2] + z));
+#pragma unroll 4
+          for (int x = 0; x < v.w[0]; ++x)
+            win[x * v.wyz + pos] = col[(int64_t)cl(v.o[0] + x) * Mp * Mp];
+        }
+        __syncthreads();
       }
-      __syncthreads();
       if (in) {
-        const int bx = j0[0] - NG - ox, by = j0[1] - NG - oy, bz = j0[2] - NG - oz;
+        const T* const wp = win + ((j0[0] - cr.lo[0]) * v.wyz + (j0[1] - cr.lo[1]) * v.w[2] +
+                                   (j0[2] - cr.lo[2]));
+        const int px = v.wyz, py = v.w[2];
         gather_force_wide<T, NG>(M, j0, fr, [&](int kx, int ky, int kz) {
-          return win[((bx + kx) * wy + by + ky) * wz + bz + kz];
+          return wp[kx * px + ky * py + kz];
         }, g);
       }
     } else if (in) {
       gather_force_wide<T, NG>(M, j0, fr, [&](int kx, int ky, int kz) {
-        return phi[((int64_t)cl(j0[0] - NG + kx) * Mp + cl(j0[1] - NG + ky)) * Mp +
-                   cl(j0[2] - NG + kz)];
+        return phi[idx3(cl(j0[0] - NG + kx), cl(j0[1] - NG + ky), cl(j0[2] - NG + kz), Mp, Mp)];
       }, g);
     }
   }
@@ -533,8 +603,7 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
   uint4* const hint = a.cells + (t.p_off / kBlock + local);
   constexpr bool kForce = MODE != kDepositOnly && MODE != kInit;
   uint4 h = make_uint4(0u, 0u, 0u, 0u);
-  // the kept extents place the fixed window of the order-2 gradient only
-  const bool use_hints = NG == 1 && a.use_hints != 0;
+  const bool use_hints = a.use_hints != 0;
   if (kForce && use_hints) h = *hint;
   // lattice site: the brick's corner from the uniform brick index, the thread's place in the
   // brick from its index (the layout of brick_site)
@@ -593,7 +662,10 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
                             (unsigned)__builtin_amdgcn_readfirstlane(h.y),
                             (unsigned)__builtin_amdgcn_readfirstlane(h.z)};
     hc = cells_decode(hq);
-    staged = stage_window_direct<T>(a.phi + t.h_off, M, hc, reinterpret_cast<T*>(win));
+    if constexpr (NG == 1)
+      staged = stage_window_direct<T>(a.phi + t.h_off, M, hc, reinterpret_cast<T*>(win));
+    else
+      staged = stage_wide_direct<T, NG>(a.phi + t.h_off, M, hc, reinterpret_cast<T*>(win));
   }
   const StepScalars sc = a.sc;
   double u[3];
@@ -621,7 +693,7 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
                      hinted, hc, staged, g);
     else
       block_force_wide<T, NG>(a.phi + t.h_off, M, u[0], u[1], u[2], reinterpret_cast<T*>(win),
-                              bounds, g);
+                              bounds, hinted, hc, staged, g);
 #pragma unroll
     for (int c = 0; c < 3; ++c) pr[c] += (T)sc.beta * (g[c] - lpt[c]);
     if (MODE == kFinalKick) {
