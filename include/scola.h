@@ -160,7 +160,9 @@ typedef struct {
   /* reverse mode (all 0 when cfg.checkpoint_every == 0); c = checkpoint_every */
   size_t ckpt;             /* R [ceil(n_steps/c)][6][P]: (x_res, p_res) before steps 0, c, ... */
   size_t seg_x;            /* R [c+1][3][P]: ring of x_res per step (slot = step mod (c+1))
-                              for the segment being reversed and the first step after it */
+                              for the segment being reversed and the first step after it;
+                              checkpointed steps are read from ckpt instead.  The forward pass
+                              fills both rings for the last segment */
   size_t seg_phi;          /* R [c+1][H]: ring of the potentials of the same steps */
   size_t lam_x, lam_p;     /* R [3][P]: adjoints of x_res and p_res */
   size_t lam_psi1, lam_psi2; /* R [3][P]: accumulated adjoints of Psi1, Psi2 */

@@ -105,7 +105,8 @@ struct ParticleArgs {
   const T* psi2;
   T* xres;
   T* xout;                  // x_res after the drift: xres itself, or another buffer
-  T* pres;
+  const T* pin;             // p_res before the kick: pres itself, or another buffer
+  T* pres;                  // p_res after it
   const T* phi;
   typename MeshFixed<T>::rho_t* rho;
   unsigned long long* dropped;

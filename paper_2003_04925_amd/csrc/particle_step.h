@@ -673,7 +673,8 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
   for (int c = 0; c < 3; ++c) u[c] = lpt_base(q[c], sc.D1, s1[c], sc.D2, s2[c]) + (double)xr[c];
   if (kForce) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) pr[c] = fresh ? T(0) : __builtin_nontemporal_load(ppr[c] + tid);
+    for (int c = 0; c < 3; ++c)
+      pr[c] = fresh ? T(0) : __builtin_nontemporal_load(a.pin + (c * P + p0) + tid);
     // the LPT terms of the kick and of the next position are formed before the force, so
     // Psi1 and Psi2 are not held across it
     const double d2 = sc.D2 - sc.D1 * sc.D1;
