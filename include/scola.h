@@ -316,11 +316,13 @@ scola_status scola_plan_schedule(const scola_plan* plan, scola_class_schedule* o
 scola_status scola_plan_set_schedule(scola_plan* plan, const scola_class_schedule* in,
                                      int32_t n_classes);
 
-/* hipGraph replay of scola_evolve (enabled by default).  With the batched schedule over all
- * tiles, the second call of scola_evolve on a workspace records the whole evolution (every
- * kernel launch and checkpoint copy) as one graph on a plan-owned capture stream, and that
- * and every later call launch the graph on `stream`.  The graph is rebuilt after a change
- * of workspace or schedule.  enable = 0 drops it and runs every call eagerly. */
+/* hipGraph replay of scola_evolve (enabled by default).  Over all tiles, the second call of
+ * scola_evolve on a workspace records the whole evolution as one graph on a plan-owned capture
+ * stream, and that and every later call launch the graph on `stream`.  The graph is rebuilt
+ * after a change of workspace or schedule.  enable = 0 drops it and runs every call eagerly.
+ * With the per-tile schedule the tiles go out over up to four streams (`stream` and plan-owned
+ * ones that fork from and join back to it), and a call whose `stream` the caller is itself
+ * capturing enqueues its launches there instead of a graph. */
 scola_status scola_plan_set_graph(scola_plan* plan, int32_t enable);
 
 /* One persistent launch per KDK step (the batching pattern of a single fused launch per
