@@ -189,34 +189,57 @@ __device__ __forceinline__ void store_split4(_Float16* bh, _Float16* bl, int o, 
   *reinterpret_cast<h4*>(bl + o) = lv;
 }
 
-// In-place unnormalised DST-I along z (rows, stride 1) and y (stride n) of the n x n plane
-// at `plane`.  `buf` (mfma_split_bytes(R), 16-byte aligned) may alias the plane: the plane
-// is read into registers before it is written.  `slots` holds 2 kWavesPerBlock floats; `s`
-// are the wave's sine fragments (load_sine, issued early by the caller so that their
-// latency overlaps its own loads).  Must be called by all threads of the block; ends with
-// a barrier.
+// Values of an n x n plane per thread: thread t holds elements t, t + kBlock, ... (zero beyond
+// n^2), so that a plane comes from global memory straight into the registers its maximum and
+// its split are formed from.
 template <int R>
-__device__ __forceinline__ void plane_dst_mfma(float* plane, _Float16* buf, float* slots,
+constexpr int plane_regs() {
+  return ((16 * R - 1) * (16 * R - 1) + kBlock - 1) / kBlock;
+}
+template <int R>
+__device__ __forceinline__ void load_plane(const float* __restrict__ src,
+                                           float (&v)[plane_regs<R>()]) {
+  constexpr int n = 16 * R - 1;
+#pragma unroll
+  for (int q = 0; q < plane_regs<R>(); ++q) {
+    const int e = q * kBlock + (int)threadIdx.x;
+    v[q] = e < n * n ? src[e] : 0.0f;
+  }
+}
+
+// Unnormalised DST-I along z (rows, stride 1) and y (stride n) of the n x n plane held in v;
+// the result goes to `plane` in LDS.  `buf` (mfma_split_bytes(R), 16-byte aligned) may alias
+// `plane`, and what the threads read there before this call must only be read before its
+// first barrier.  `slots` holds 2 kWavesPerBlock floats; `s` are the wave's sine fragments
+// (load_sine, issued early by the caller so that their latency overlaps its own loads).  Must
+// be called by all threads of the block; ends with a barrier.
+template <int R>
+__device__ __forceinline__ void plane_dst_mfma(const float (&v)[plane_regs<R>()], float* plane,
+                                               _Float16* buf, float* slots,
                                                const SineFrag<R>& s) {
   using D = MfmaDst<R>;
   constexpr int n = D::n, M = D::M, K = D::K, KP = D::KP;
   _Float16* const bh = buf;
   _Float16* const bl = buf + M * KP;
-  // the plane (zero beyond n x n, up to M lines of K values) in registers, and its maximum
-  constexpr int kElems = M * K, kPer = (kElems + kBlock - 1) / kBlock;
-  float v[kPer];
   float m = 0.0f;
 #pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int e = q * kBlock + (int)threadIdx.x, y = e / K, z = e - (e / K) * K;
-    v[q] = (e < kElems && y < n && z < n) ? plane[y * n + z] : 0.0f;
-    m = fmaxf(m, fabsf(v[q]));
+  for (int q = 0; q < plane_regs<R>(); ++q) m = fmaxf(m, fabsf(v[q]));
+  const float s1 = pow2_scale(block_max_abs(m, slots));   // its barrier frees the split lines
+  // the lines' padding: columns n .. K - 1 of every line, and line n (M = n + 1)
+  for (int i = threadIdx.x; i < M * (K - n) + n; i += kBlock) {
+    const int y = i < M * (K - n) ? i / (K - n) : n;
+    const int z = i < M * (K - n) ? n + i - y * (K - n) : i - M * (K - n);
+    bh[y * KP + z] = (_Float16)0.0f;
+    bl[y * KP + z] = (_Float16)0.0f;
   }
-  const float s1 = pow2_scale(block_max_abs(m, slots));   // its barrier ends the plane reads
+  // the rows and columns are formed here: a caller that needs them too would otherwise keep
+  // them in registers, one per value, from there to here
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
 #pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int e = q * kBlock + (int)threadIdx.x, y = e / K, z = e - (e / K) * K;
-    if (e < kElems) split_half(v[q] * s1, bh[y * KP + z], bl[y * KP + z]);
+  for (int q = 0; q < plane_regs<R>(); ++q) {
+    const int e = q * kBlock + tid, y = e / n, z = e - y * n;
+    if (e < n * n) split_half(v[q] * s1, bh[y * KP + z], bl[y * KP + z]);
   }
   __syncthreads();
   // along z: A[y][kz] = sum_z Y[y][z] S[kz][z]

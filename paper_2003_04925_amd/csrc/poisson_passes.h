@@ -562,15 +562,22 @@ __device__ __forceinline__ unsigned long long* found_slots(unsigned char* smem) 
   return reinterpret_cast<unsigned long long*>(smem + 32);
 }
 
-// The unnormalised 2-D DST-I of a pass's n x n plane in LDS: on the matrix cores for FP32
-// plans (split lines aliasing the plane, slots at the start of smem), else by the FFT with
-// the twiddles at the start of smem.
+// The unnormalised 2-D DST-I of a pass's n x n plane, result in LDS: for FP32 plans on the
+// matrix cores from the registers v (split lines aliasing the plane, slots at the start of
+// smem), else by the FFT in LDS with the twiddles at the start of smem.
 template <typename T, int R>
-__device__ __forceinline__ void plane_transform(T* plane, unsigned char* smem,
+struct PlaneValues {};
+template <int R>
+struct PlaneValues<float, R> {
+  float v[plane_regs<R>()];
+};
+template <typename T, int R>
+__device__ __forceinline__ void plane_transform(const PlaneValues<T, R>& pv, T* plane,
+                                                unsigned char* smem,
                                                 const PlaneOperands<T, R>& op) {
   if constexpr (std::is_same<T, float>::value)
-    plane_dst_mfma<R>(plane, reinterpret_cast<_Float16*>(plane), reinterpret_cast<float*>(smem),
-                      op.s);
+    plane_dst_mfma<R>(pv.v, plane, reinterpret_cast<_Float16*>(plane),
+                      reinterpret_cast<float*>(smem), op.s);
   else
     plane_dst<R, T>(plane, reinterpret_cast<const cx<T>*>(smem));
 }
@@ -603,18 +610,26 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
   T* plane = reinterpret_cast<T*>(smem + (kMfma ? kMfmaHead : 2 * M * sizeof(cx<T>)));
   if constexpr (!kMfma) load_twiddles(tw, a, t);
   PlaneOperands<T, R> op;
+  PlaneValues<T, R> pv;
   const int64_t base = t.g_off + (int64_t)x * n * n;
   const double* bc = a.bc0 + t.h_off;
   const double D1 = a.D1_bc;
   if constexpr (ADJ) {
     op.load(a, t);
     const T* const wk = a.work + base;
+    if constexpr (kMfma) {
+      load_plane<R>(wk, pv.v);
+    } else {
 #pragma unroll 8
-    for (int e = threadIdx.x; e < n * n; e += blockDim.x) plane[e] = wk[e];
+      for (int e = threadIdx.x; e < n * n; e += blockDim.x) plane[e] = wk[e];
+    }
   } else {
     using Rho = typename MeshFixed<T>::rho_t;
     Rho* const rp = a.rho + base;   // the plane's first node (block-uniform)
-    constexpr int kBatch = 16;   // independent loads in flight per thread
+    // independent loads in flight per thread: the plane's values in one batch up to 64^3, in
+    // two for larger boxes
+    constexpr int kVals = (n * n + kBlock - 1) / kBlock;
+    constexpr int kBatch = !kMfma ? 16 : R <= 4 ? kVals : (kVals + 1) / 2;
     constexpr double kUnit = 1.0 / (double)(1ll << MeshFixed<T>::bits);
     // delta' = delta - Delta Phi_BCs (App. C.1): an interior node next to a face takes
     // D1 Phi_BC^0 of its face-layer neighbour (padded index = node index + 1; interior node
@@ -786,7 +801,7 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
       if (pe >= 0) plane[pe] = (T)((double)plane[pe] - D1 * pterm);
     }
   }
-  __syncthreads();
+  if constexpr (!(ADJ && kMfma)) __syncthreads();
   if constexpr (!ADJ && std::is_same<T, float>::value) {
     if (threadIdx.x == 0) {
       unsigned long long f = 0;
@@ -795,7 +810,10 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
       if (f != 0ull) atomicAdd(a.kept + m.tile[b], f);
     }
   }
-  plane_transform<T, R>(plane, smem, op);
+  // the forward pass makes its corrections in LDS: with the values held in registers from the
+  // mass on, as in the third pass, it was slower (64^3 56 -> 58 us, 112^3 216 -> 251 us)
+  if constexpr (!ADJ && kMfma) load_plane<R>(plane, pv.v);
+  plane_transform<T, R>(pv, plane, smem, op);
   T* const wk = a.work + base;
   for (int e = threadIdx.x; e < n * n; e += blockDim.x) wk[e] = plane[e];
 }
@@ -956,8 +974,13 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
     }
   }
   const T* const wk = a.work + base;
+  PlaneValues<T, R> pv;
+  if constexpr (kMfma) {
+    load_plane<R>(wk, pv.v);
+  } else {
 #pragma unroll 8
-  for (int e = threadIdx.x; e < n * n; e += blockDim.x) plane[e] = wk[e];
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) plane[e] = wk[e];
+  }
   // order 2, evolution: the first pass of the next solve takes this plane's perimeter terms
   // (the same padded plane A's face-layer values, which bval holds) from its `work` plane;
   // they are summed in LDS right behind the n x n plane (for FP32 plans inside the region
@@ -1016,7 +1039,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
     double* const out = handoff_terms(a.work + base);
     for (int i = threadIdx.x; i < 4 * (n - 1); i += blockDim.x) out[i] = pacc[i];
   }
-  plane_transform<T, R>(plane, smem, op);
+  plane_transform<T, R>(pv, plane, smem, op);
   if constexpr (ADJ) {
     // lam_rho = lam_delta', and the plane of `work` is cleared (the next reverse step
     // accumulates into a zeroed source)
