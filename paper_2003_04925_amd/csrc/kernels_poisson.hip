@@ -31,43 +31,60 @@ namespace scola {
 namespace {
 
 // Waves per SIMD the FP32 passes are compiled for: their matrix-core transforms leave them
-// latency-bound, so boxes up to 64^3 ask for full occupancy (at most 64 registers a lane),
-// and boxes of 80^3 for the 4 that their LDS allows (c3: 1.01 -> 0.98 ms per solve); at
-// 96^3 that would spill (c5: 4.25 -> 4.68 ms), so larger boxes and FP64 plans take what
-// their registers allow.  The 64^3 reverse passes and the first passes of 64^3 and 48^3
-// at orders 4 and 6 need a few more registers than 64: they take 7 waves (72 registers) rather
-// than spill to scratch.
+// latency-bound, so boxes up to 64^3 ask for full occupancy (at most 64 registers a lane), and
+// so does the first pass of 80^3 at order 2 (16 boxes: 125 -> 107 us).  The other passes of
+// larger boxes would spill (first pass of 96^3, 512 boxes: 1324 -> 1716 us, pencils 965 ->
+// 1344), so they and FP64 plans take what their registers allow.  The 64^3 reverse passes and
+// the passes of 64^3 and 48^3 at orders 4 and 6 need a few more registers than 64: they take 7
+// waves (72 registers) rather than spill to scratch.
 template <typename T, int R, bool ADJ = false, int NG = 1>
 constexpr int pass_waves() {
   if (!std::is_same<T, float>::value) return 1;
   if ((R == 4 && (ADJ || NG > 1)) || (R == 3 && NG > 1)) return 7;
-  return R <= 4 ? 8 : R == 5 ? 4 : 1;
+  return R <= 4 ? 8 : 1;
+}
+template <typename T, int R, bool ADJ, int NG>
+constexpr int first_pass_waves() {
+  return std::is_same<T, float>::value && R == 5 && NG == 1 ? 8 : pass_waves<T, R, ADJ, NG>();
+}
+
+// Threads of a block.  The FP32 passes above 64^3 have more 16-row tiles of the sine matrix than
+// a block of 256 has waves: with 512, each wave has one tile, half the values in flight per
+// thread and so fewer registers, and more waves fit a CU (512 boxes of 96^3: first pass 1362 ->
+// 1324 us, pencils 1109 -> 965, third 1042 -> 1080; 29 of 112^3: 222 -> 163, 121 -> 107, 167 ->
+// 128; 80^3: 138 -> 125, 99 -> 85, 114 -> 99).  64 R threads, where no wave is idle in the
+// products, were slower (96^3: 1522, 1049 and 1244 us): six or seven waves do not spread evenly
+// over the four SIMDs.
+template <typename T, int R>
+constexpr int pass_threads() {
+  return std::is_same<T, float>::value && R >= 5 ? 512 : kBlock;
 }
 
 template <typename T, int R, bool ADJ, int NG>
-__global__ void __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(pass_waves<T, R, ADJ, NG>())))
+__global__ void __launch_bounds__((pass_threads<T, R>()))
+__attribute__((amdgpu_waves_per_eu(first_pass_waves<T, R, ADJ, NG>())))
 k_poisson_p1(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p1_block<T, R, ADJ, NG>(a, m, L, smem);
+  if (L < m.count) poisson_p1_block<T, R, ADJ, NG, pass_threads<T, R>()>(a, m, L, smem);
 }
 
 template <typename T, int R>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(pass_waves<T, R>())))
+__global__ void __launch_bounds__((pass_threads<T, R>()))
+__attribute__((amdgpu_waves_per_eu(pass_waves<T, R>())))
 k_poisson_p2(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p2_block<T, R>(a, m, L, smem);
+  if (L < m.count) poisson_p2_block<T, R, pass_threads<T, R>()>(a, m, L, smem);
 }
 
 template <typename T, int R, bool ADJ, int NG>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__((pass_threads<T, R>()))
 __attribute__((amdgpu_waves_per_eu(pass_waves<T, R, ADJ, NG>())))
 k_poisson_p3(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p3_block<T, R, ADJ, NG>(a, m, L, smem);
+  if (L < m.count) poisson_p3_block<T, R, ADJ, NG, pass_threads<T, R>()>(a, m, L, smem);
 }
 
 }  // namespace
@@ -77,8 +94,8 @@ k_poisson_p3(MeshArgs<T> a, BlockMap m) {
 // perimeter terms it hands on; FP32 plans the block-maximum slots, then the plane region
 // (the plane or the split lines aliasing it, whose tail beyond the plane holds P3's
 // perimeter terms before the transform), P2 the eigenvalues and the chunk's split lines
-// aliased by its output tile.  P3 holds the padded plane's border in registers.  Sized per
-// M and per pass, so small boxes keep more blocks per CU.
+// aliased by its output tile.  P3 holds the padded plane's border in registers.  Sized per M
+// and per pass, so small boxes keep more blocks per CU.
 template <typename T>
 size_t poisson_lds_bytes(int M, int pass, int ng) {
   (void)ng;
@@ -90,11 +107,12 @@ size_t poisson_lds_bytes(int M, int pass, int ng) {
     // split lines that alias it); P2: the eigenvalues, then the split lines of the chunk's
     // columns aliased by the output tile
     const int R = M / 16;
+    const size_t head = R >= 5 ? mfma_head<512>() : mfma_head<kBlock>();
     const size_t region = std::max(n * n * sizeof(float), mfma_split_bytes(R));
-    if (pass == 1 || pass == 3) return kMfmaHead + region;
+    if (pass == 1 || pass == 3) return head + region;
     const size_t lines =
         (size_t)kPencilChunkMfma * (32 * ((R + 1) / 2) + 8) * 2 * sizeof(_Float16);
-    return kMfmaHead + (size_t)M * sizeof(float) +
+    return head + (size_t)M * sizeof(float) +
            std::max(n * (kPencilChunkMfma + 1) * sizeof(float), lines);
   }
   if (pass == 1) return tw + n * n * sizeof(T);
@@ -130,13 +148,14 @@ hipError_t launch_poisson_R(const MeshArgs<T>& a, const BlockMap& p1, const Bloc
       done.fetch_or(bit);
     }
   }
+  const dim3 block(pass_threads<T, R>());
   if (p1.count > 0)
-    hipLaunchKernelGGL((k_poisson_p1<T, R, ADJ, NG>), dim3(padded_grid(p1)), dim3(kBlock), l1, s,
+    hipLaunchKernelGGL((k_poisson_p1<T, R, ADJ, NG>), dim3(padded_grid(p1)), block, l1, s,
                        a, p1);
   if (p2.count > 0)
-    hipLaunchKernelGGL((k_poisson_p2<T, R>), dim3(padded_grid(p2)), dim3(kBlock), l2, s, a, p2);
+    hipLaunchKernelGGL((k_poisson_p2<T, R>), dim3(padded_grid(p2)), block, l2, s, a, p2);
   if (p3.count > 0)
-    hipLaunchKernelGGL((k_poisson_p3<T, R, ADJ, NG>), dim3(padded_grid(p3)), dim3(kBlock), l3, s,
+    hipLaunchKernelGGL((k_poisson_p3<T, R, ADJ, NG>), dim3(padded_grid(p3)), block, l3, s,
                        a, p3);
   return hipGetLastError();
 }

@@ -501,15 +501,15 @@ __device__ __forceinline__ constexpr double lap_weight(int k) {
 
 // What a pass's plane transform needs in registers: the wave's sine fragments for FP32
 // plans (requested at the start of the pass), nothing for the FFT.
-template <typename T, int R>
+template <typename T, int R, int NT>
 struct PlaneOperands {
   __device__ void load(const MeshArgs<T>&, const TileDesc&) {}
 };
-template <int R>
-struct PlaneOperands<float, R> {
-  SineFrag<R> s;
+template <int R, int NT>
+struct PlaneOperands<float, R, NT> {
+  SineFrag<R, NT> s;
   __device__ void load(const MeshArgs<float>& a, const TileDesc& t) {
-    s = load_sine<R>(reinterpret_cast<const _Float16*>(a.sine) + t.dm_off);
+    s = load_sine<R, NT>(reinterpret_cast<const _Float16*>(a.sine) + t.dm_off);
   }
 };
 
@@ -556,32 +556,34 @@ __device__ __forceinline__ double* handoff_terms(T* plane) {
 }
 
 // FP32 plans, first pass: the waves' sums of the plane's mass, in the LDS head behind the
-// block-maximum slots of the transform (which use its first 2 kBlock / 64 floats).
+// block-maximum slots of the transform (which use its first 2 NT / 64 floats).
+template <int NT>
 __device__ __forceinline__ unsigned long long* found_slots(unsigned char* smem) {
-  static_assert(kMfmaHead >= 32 + 8 * (kBlock / 64), "LDS head holds both slot sets");
-  return reinterpret_cast<unsigned long long*>(smem + 32);
+  static_assert(mfma_head<NT>() >= 16 * (NT / 64), "LDS head holds both slot sets");
+  return reinterpret_cast<unsigned long long*>(smem + 8 * (NT / 64));
 }
 
 // The unnormalised 2-D DST-I of a pass's n x n plane, result in LDS: for FP32 plans on the
 // matrix cores from the registers v (split lines aliasing the plane, slots at the start of
 // smem), else by the FFT in LDS with the twiddles at the start of smem.
-template <typename T, int R>
+template <typename T, int R, int NT>
 struct PlaneValues {};
-template <int R>
-struct PlaneValues<float, R> {
-  float v[plane_regs<R>()];
+template <int R, int NT>
+struct PlaneValues<float, R, NT> {
+  float v[plane_regs<R, NT>()];
 };
-template <typename T, int R>
-__device__ __forceinline__ void plane_transform(const PlaneValues<T, R>& pv, T* plane,
+template <typename T, int R, int NT>
+__device__ __forceinline__ void plane_transform(const PlaneValues<T, R, NT>& pv, T* plane,
                                                 unsigned char* smem,
-                                                const PlaneOperands<T, R>& op) {
-  if constexpr (std::is_same<T, float>::value)
-    plane_dst_mfma<R>(pv.v, plane, reinterpret_cast<_Float16*>(plane),
-                      reinterpret_cast<float*>(smem), op.s);
-  else
+                                                const PlaneOperands<T, R, NT>& op) {
+  if constexpr (std::is_same<T, float>::value) {
+    plane_dst_mfma<R, NT, true>(pv.v, plane, reinterpret_cast<_Float16*>(plane),
+                                reinterpret_cast<float*>(smem), op.s);
+    __syncthreads();
+  } else {
     plane_dst<R, T>(plane, reinterpret_cast<const cx<T>*>(smem));
+  }
 }
-
 // Floats of a pass's plane region: the n x n plane, or for FP32 plans the larger of it and
 // the split lines that alias it.
 template <typename T, int R>
@@ -596,7 +598,7 @@ __host__ __device__ constexpr size_t plane_region_elems() {
 // NG: ghost layers of the finite-difference order 2 NG (Sec. 3): the box's Phi_BC^0 and
 // potential live on the padded nodes [-NG, M + NG]^3 (padded index = node + NG), and
 // Phi_BCs occupies the NG layers outside the interior on each side.
-template <typename T, int R, bool ADJ, int NG = 1>
+template <typename T, int R, bool ADJ, int NG = 1, int NT = kBlock>
 __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const BlockMap& m, int L,
                                                  unsigned char* smem) {
   static_assert(!ADJ || NG == 1, "the reverse passes exist for order 2 only");
@@ -607,10 +609,10 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
   // FP32 plans transform on the matrix cores (no twiddles: the block-maximum slots lead)
   constexpr bool kMfma = std::is_same<T, float>::value;
   cx<T>* tw = reinterpret_cast<cx<T>*>(smem);
-  T* plane = reinterpret_cast<T*>(smem + (kMfma ? kMfmaHead : 2 * M * sizeof(cx<T>)));
+  T* plane = reinterpret_cast<T*>(smem + (kMfma ? mfma_head<NT>() : 2 * M * sizeof(cx<T>)));
   if constexpr (!kMfma) load_twiddles(tw, a, t);
-  PlaneOperands<T, R> op;
-  PlaneValues<T, R> pv;
+  PlaneOperands<T, R, NT> op;
+  PlaneValues<T, R, NT> pv;
   const int64_t base = t.g_off + (int64_t)x * n * n;
   const double* bc = a.bc0 + t.h_off;
   const double D1 = a.D1_bc;
@@ -618,7 +620,7 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
     op.load(a, t);
     const T* const wk = a.work + base;
     if constexpr (kMfma) {
-      load_plane<R>(wk, pv.v);
+      load_plane<R, NT>(wk, pv.v);
     } else {
 #pragma unroll 8
       for (int e = threadIdx.x; e < n * n; e += blockDim.x) plane[e] = wk[e];
@@ -626,10 +628,10 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
   } else {
     using Rho = typename MeshFixed<T>::rho_t;
     Rho* const rp = a.rho + base;   // the plane's first node (block-uniform)
-    // independent loads in flight per thread: the plane's values in one batch up to 64^3, in
-    // two for larger boxes
-    constexpr int kVals = (n * n + kBlock - 1) / kBlock;
-    constexpr int kBatch = !kMfma ? 16 : R <= 4 ? kVals : (kVals + 1) / 2;
+    // independent loads in flight per thread: the plane's values in one batch, or in
+    // two where a thread has more than 18
+    constexpr int kVals = (n * n + NT - 1) / NT;
+    constexpr int kBatch = !kMfma ? 16 : kVals <= 18 ? kVals : (kVals + 1) / 2;
     constexpr double kUnit = 1.0 / (double)(1ll << MeshFixed<T>::bits);
     // delta' = delta - Delta Phi_BCs (App. C.1): an interior node next to a face takes
     // D1 Phi_BC^0 of its face-layer neighbour (padded index = node index + 1; interior node
@@ -657,7 +659,7 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
     // latencies overlap (order 4, 64 boxes of 64^3: 137 us a pass with the terms fetched node
     // by node after it, now 79); the 2 NG planes near an x face add the x terms everywhere
     // else in coalesced batches.
-    constexpr int kBand = NG > 1 ? (band_count<NG>(n) + kBlock - 1) / kBlock : 1;
+    constexpr int kBand = NG > 1 ? (band_count<NG>(n) + NT - 1) / NT : 1;
     int be[kBand];
     double bterm[kBand];
     auto wide_x = [&](int jy, int jz, int k) {
@@ -670,7 +672,7 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
     if constexpr (NG > 1) {
 #pragma unroll
       for (int q = 0; q < kBand; ++q) {
-        const int i = q * kBlock + (int)threadIdx.x;
+        const int i = q * NT + (int)threadIdx.x;
         be[q] = -1;
         bterm[q] = 0.0;
         if (i < band_count<NG>(n)) {
@@ -710,23 +712,23 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
     unsigned long long drop = 0;
     if constexpr (std::is_same<T, float>::value) {
       unsigned* const hw = a.hints + (t.p_off / kBlock) * 4 + 3;
-      for (int e = f0 + (int)threadIdx.x; e < f1; e += kBlock) {
+      for (int e = f0 + (int)threadIdx.x; e < f1; e += NT) {
         drop += hw[4 * e];
         hw[4 * e] = 0u;
       }
     }
     unsigned long long found = 0;   // FP32 plans: the plane's total mass in units
     unsigned near = 0;              // FP32 plans: node masses within a factor 2 of wrapping
-    for (int e0 = 0; e0 < n * n; e0 += kBatch * kBlock) {
+    for (int e0 = 0; e0 < n * n; e0 += kBatch * NT) {
       Rho r[kBatch];
 #pragma unroll
       for (int q = 0; q < kBatch; ++q) {
-        const int e = e0 + q * kBlock + threadIdx.x;
+        const int e = e0 + q * NT + threadIdx.x;
         r[q] = e < n * n ? rp[e] : Rho(0);
       }
 #pragma unroll
       for (int q = 0; q < kBatch; ++q) {
-        const int e = e0 + q * kBlock + threadIdx.x;
+        const int e = e0 + q * NT + threadIdx.x;
         if (e >= n * n) continue;
         rp[e] = Rho(0);
         if constexpr (std::is_same<T, float>::value) {
@@ -753,7 +755,7 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
       // before the transform)
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) found += __shfl_xor(found, d);
-      if ((threadIdx.x & 63) == 0) found_slots(smem)[threadIdx.x >> 6] = found;
+      if ((threadIdx.x & 63) == 0) found_slots<NT>(smem)[threadIdx.x >> 6] = found;
       if ((int)(threadIdx.x & ~63u) < f1 - f0) {
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) drop += __shfl_xor(drop, d);
@@ -806,16 +808,21 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
     if (threadIdx.x == 0) {
       unsigned long long f = 0;
 #pragma unroll
-      for (int w = 0; w < kBlock / 64; ++w) f += found_slots(smem)[w];
+      for (int w = 0; w < NT / 64; ++w) f += found_slots<NT>(smem)[w];
       if (f != 0ull) atomicAdd(a.kept + m.tile[b], f);
     }
   }
   // the forward pass makes its corrections in LDS: with the values held in registers from the
   // mass on, as in the third pass, it was slower (64^3 56 -> 58 us, 112^3 216 -> 251 us)
-  if constexpr (!ADJ && kMfma) load_plane<R>(plane, pv.v);
-  plane_transform<T, R>(pv, plane, smem, op);
+  if constexpr (!ADJ && kMfma) load_plane<R, NT>(plane, pv.v);
   T* const wk = a.work + base;
-  for (int e = threadIdx.x; e < n * n; e += blockDim.x) wk[e] = plane[e];
+  if constexpr (kMfma && direct_stores(R)) {
+    plane_dst_mfma<R, NT, false>(pv.v, wk, reinterpret_cast<_Float16*>(plane),
+                                 reinterpret_cast<float*>(smem), op.s);
+  } else {
+    plane_transform<T, R, NT>(pv, plane, smem, op);
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) wk[e] = plane[e];
+  }
 }
 
 // The cw <= kPencilChunk x pencils p0 .. p0 + cw - 1 (pencil p = n y + z) staged in `tile`
@@ -844,7 +851,7 @@ __device__ __forceinline__ void pencil_solve(T* tile, int cw, int p0, const T* e
   __syncthreads();
 }
 
-template <typename T, int R>
+template <typename T, int R, int NT = kBlock>
 __device__ __forceinline__ void poisson_p2_block(const MeshArgs<T>& a, const BlockMap& m, int L,
                                                  unsigned char* smem) {
   const int b = m.base + L;
@@ -855,7 +862,7 @@ __device__ __forceinline__ void poisson_p2_block(const MeshArgs<T>& a, const Blo
   // chunk's nodes of one x plane are C consecutive words
   const int p0 = m.local[b] * C, cw = min(C, n * n - p0);
   if constexpr (std::is_same<T, float>::value) {
-    pencils_mfma<R>(a.work + t.g_off + p0, p0, cw, a.eigen + t.ev_off,
+    pencils_mfma<R, NT>(a.work + t.g_off + p0, p0, cw, a.eigen + t.ev_off,
                     reinterpret_cast<const _Float16*>(a.sine) + t.dm_off, smem);
     return;
   }
@@ -887,7 +894,7 @@ __device__ __forceinline__ void poisson_p2_block(const MeshArgs<T>& a, const Blo
   }
 }
 
-template <typename T, int R, bool ADJ, int NG = 1>
+template <typename T, int R, bool ADJ, int NG = 1, int NT = kBlock>
 __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const BlockMap& m, int L,
                                                  unsigned char* smem) {
   static_assert(!ADJ || NG == 1, "the reverse passes exist for order 2 only");
@@ -916,9 +923,9 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
   }
   constexpr bool kMfma = std::is_same<T, float>::value;
   cx<T>* tw = reinterpret_cast<cx<T>*>(smem);
-  T* plane = reinterpret_cast<T*>(smem + (kMfma ? kMfmaHead : 2 * M * sizeof(cx<T>)));
+  T* plane = reinterpret_cast<T*>(smem + (kMfma ? mfma_head<NT>() : 2 * M * sizeof(cx<T>)));
   if constexpr (!kMfma) load_twiddles(tw, a, t);
-  PlaneOperands<T, R> op;
+  PlaneOperands<T, R, NT> op;
   op.load(a, t);
   const int x = local;
   const int64_t base = t.g_off + (int64_t)x * n * n;
@@ -928,7 +935,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
   // registers until the plane is written.  Border element i: rows 0..NG and M+NG..M+2NG
   // whole, then columns 0..NG and M+NG..M+2NG of the rows in between.
   constexpr int kBorder = Mp * Mp - n * n;
-  constexpr int kPerThread = (kBorder + kBlock - 1) / kBlock;
+  constexpr int kPerThread = (kBorder + NT - 1) / NT;
   constexpr int kW = 2 * (NG + 1);   // border rows, and border columns per inner row
   auto border_offset = [](int i) {
     int B, C;
@@ -947,7 +954,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
   if constexpr (!ADJ) {
 #pragma unroll
     for (int q = 0; q < kPerThread; ++q) {
-      const int i = q * kBlock + threadIdx.x;
+      const int i = q * NT + threadIdx.x;
       bval[q] = i < kBorder ? bc[(int64_t)A * Mp * Mp + border_offset(i)] : 0.0;
     }
   }
@@ -974,9 +981,9 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
     }
   }
   const T* const wk = a.work + base;
-  PlaneValues<T, R> pv;
+  PlaneValues<T, R, NT> pv;
   if constexpr (kMfma) {
-    load_plane<R>(wk, pv.v);
+    load_plane<R, NT>(wk, pv.v);
   } else {
 #pragma unroll 8
     for (int e = threadIdx.x; e < n * n; e += blockDim.x) plane[e] = wk[e];
@@ -999,7 +1006,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
   if constexpr (!ADJ) {
 #pragma unroll
     for (int q = 0; q < kPerThread; ++q) {
-      const int i = q * kBlock + threadIdx.x;
+      const int i = q * NT + threadIdx.x;
       if (i < kBorder) bv[q] = (T)(D1 * bval[q]);
       // rows B = 1 and B = M + 1: the y faces of interior rows y = 0 and y = n - 1
       if (hand_out && i >= Mp && i < 3 * Mp) {
@@ -1010,7 +1017,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
     if (a.ov_phi) {
 #pragma unroll
       for (int q = 0; q < kPerThread; ++q) {
-        const int i = q * kBlock + threadIdx.x;
+        const int i = q * NT + threadIdx.x;
         if (i < kBorder) {
           const int o = border_offset(i);
           bv[q] = full_at(a.ov_phi, a.ov_N, t, A - NG, o / Mp - NG, o - (o / Mp) * Mp - NG);
@@ -1024,7 +1031,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
     // added to the y face's value at the four corners
 #pragma unroll
     for (int q = 0; q < kPerThread; ++q) {
-      const int i = q * kBlock + threadIdx.x;
+      const int i = q * NT + threadIdx.x;
       if (i >= 4 * Mp && i < kBorder) {
         const int j = i - 4 * Mp, y = j >> 2, c = j & 3;
         if (c == 1 || c == 2) {
@@ -1039,7 +1046,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
     double* const out = handoff_terms(a.work + base);
     for (int i = threadIdx.x; i < 4 * (n - 1); i += blockDim.x) out[i] = pacc[i];
   }
-  plane_transform<T, R>(pv, plane, smem, op);
+  plane_transform<T, R, NT>(pv, plane, smem, op);
   if constexpr (ADJ) {
     // lam_rho = lam_delta', and the plane of `work` is cleared (the next reverse step
     // accumulates into a zeroed source)
@@ -1087,7 +1094,7 @@ __device__ __forceinline__ void poisson_p3_block(const MeshArgs<T>& a, const Blo
   }
 #pragma unroll
   for (int q = 0; q < kPerThread; ++q) {
-    const int i = q * kBlock + threadIdx.x;
+    const int i = q * NT + threadIdx.x;
     if (i < kBorder) out[border_offset(i)] = bv[q];
   }
 }
