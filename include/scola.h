@@ -280,10 +280,12 @@ scola_status scola_evolve_overrides(scola_plan* plan, const void* d_delta, const
  *   waves_per_simd       6 or 8: register budget the fused particle kernel is compiled for
  *                        (6 = 80 registers, 8 = 64; FP64 plans need more than 64 and run
  *                        at the occupancy their registers allow);
- *   xcd_remap_particles  1: blocks numbered so each of the 8 XCDs takes a contiguous run of
- *                        whole boxes (their meshes stay in one L2); 0: hardware order;
- *   xcd_remap_mesh       the same for the three Poisson passes.
- * Defaults {6, 1, 1}.  scola_plan_tune times the choices per class on the workspace's
+ *   xcd_remap_particles  1: blocks numbered so runs of four neighbouring bricks go to the 8
+ *                        XCDs in turn (FP64 plans: so each XCD takes a contiguous run of
+ *                        whole boxes); 0: hardware order;
+ *   xcd_remap_mesh       1: blocks of the three Poisson passes numbered so each XCD takes a
+ *                        contiguous run of whole boxes (their meshes stay in one L2).
+ * Defaults {8, 1, 1}.  scola_plan_tune times the choices per class on the workspace's
  * particles (after scola_setup, else SCOLA_ESTATE) with `reps` launches each (1..1000) and
  * keeps the fastest; it leaves the set-up fields (Psi, Phi_BC^0) untouched, clears its
  * deposits, and synchronises the stream (call it before scola_evolve, never inside a timed

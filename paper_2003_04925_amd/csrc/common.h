@@ -95,6 +95,15 @@ __device__ __forceinline__ double lane_xor(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// The value of the lane mirrored inside 8 (S = 4) or 16 (S = 8) lanes: within a reduction
+// whose groups of S lanes already agree it is the other group's value, as lane_xor<S> would
+// give it, in one exchange instead of two.
+template <int S>
+__device__ __forceinline__ int lane_mirror(int v) {
+  static_assert(S == 4 || S == 8, "group size");
+  return __builtin_amdgcn_mov_dpp(v, S == 4 ? 0x141 : 0x140, 0xF, 0xF, true);
+}
+
 // Particles of a box are stored brick by brick: bricks of 4 x 8 x 8 lattice sites (256
 // particles, one thread block), bricks in lattice order, sites inside a brick in lattice
 // order.  A block's particles therefore form a compact Lagrangian cube (small Eulerian

@@ -101,8 +101,8 @@ template <int NT>
 __device__ __forceinline__ float block_max_abs(float m, float* slots) {
   m = fmaxf(m, lane_xor<1>(m));
   m = fmaxf(m, lane_xor<2>(m));
-  m = fmaxf(m, lane_xor<4>(m));
-  m = fmaxf(m, lane_xor<8>(m));
+  m = fmaxf(m, __int_as_float(lane_mirror<4>(__float_as_int(m))));
+  m = fmaxf(m, __int_as_float(lane_mirror<8>(__float_as_int(m))));
   const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 0));
   const float b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 16));
   const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 32));

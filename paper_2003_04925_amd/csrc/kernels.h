@@ -11,12 +11,18 @@ namespace scola {
 // Block map of one batched launch: block b works on tile blk_tile[b], local unit
 // blk_local[b] (a particle block of 256, a plane, or a pencil chunk).  Blocks of one tile
 // are contiguous, so a per-tile launch is a sub-range [base, base + count).
+// Block numberings (the hardware deals consecutive workgroups to the 8 XCDs in turn): as dealt;
+// each XCD a contiguous range of logical blocks (whole boxes); or runs of kXcdRun consecutive
+// logical blocks dealt to the XCDs in turn.
+enum XcdMap : int { kXcdNone = 0, kXcdRanges = 1, kXcdRuns = 2 };
+constexpr int kXcdRun = 4;
+
 struct BlockMap {
   const int* tile = nullptr;
   const int* local = nullptr;
   int base = 0;
   int count = 0;
-  int xcd_remap = 1;       // spread consecutive logical blocks over one XCD (see kernels)
+  int xcd_remap = kXcdRanges;   // how blocks are numbered over the XCDs
 };
 
 // Per-plan tables of the periodic solves on an N^3 grid (kernels_fft.hip): exp(-2 pi i m / N),

@@ -22,9 +22,9 @@ namespace {
 // flight at once; N is a power of two, so the periodic index is a mask).  Bound by memory: 48
 // bytes stored per particle in FP32 and about 40 read.  The stores are streams as large as
 // the evolution's state, so they bypass the caches, where neighbouring bricks find each
-// other's nodes as long as one XCD takes contiguous bricks: for the 80 million particles of
-// the mixed 256^3 tiling 1.48 ms before, 1.65 with cached stores, 1.57 with bricks dealt out
-// over the XCDs, 1.17 so.
+// other's nodes; an XCD takes runs of four of them (kXcdRuns): for the 80 million particles of
+// the mixed 256^3 tiling 1.48 ms before, 1.65 with cached stores, 1.57 with single bricks dealt
+// out over the XCDs, 1.17 with a contiguous range for each, 1.12 so.
 template <typename T, int NG>
 __global__ void __launch_bounds__(kBlock)
 k_extract_psi(const TileDesc* __restrict__ tiles, BlockMap m, const double* __restrict__ phi1,
@@ -261,6 +261,7 @@ void launch_psi(const BoxSetupArgs& a, T* xres, T* pres, hipStream_t s) {
   m.tile = a.blk_tile;
   m.local = a.blk_first;
   m.count = a.n_blocks;
+  if (a.N == a.Np) m.xcd_remap = kXcdRuns;
   const dim3 grid(padded_grid(m)), block(kBlock);
   if (a.N == a.Np)
     hipLaunchKernelGGL((k_extract_psi<T, NG>), grid, block, 0, s, a.tiles, m, a.phi1, a.phi2,

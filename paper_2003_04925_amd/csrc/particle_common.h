@@ -12,19 +12,28 @@
 namespace scola {
 namespace {
 
-// Logical block index: hardware dispatches consecutive workgroups round-robin over the 8
-// XCDs, so logical = (b % 8) * (grid / 8) + b / 8 gives each XCD a contiguous run of
-// logical blocks (whole boxes).
+// Logical block index under the map's numbering; the grid is padded to whole ranges or runs.
+// Ranges keep a box's mesh in one L2; they serve the Poisson and the reverse passes best.  The
+// particle step and the extraction of Psi stream 18 and 6 arrays from memory, and eight XCDs
+// far apart in each of them reach less of its bandwidth than XCDs that advance together: runs
+// of four bricks, neighbours along z with their shared window nodes, are faster than ranges and
+// than single blocks (evolution of 64 boxes of 64^3: 8.44 against 8.65 and 8.66 ms, runs of 8
+// 8.54, of 2 8.60; 64 boxes of 96^3: 30.45 against 32.26 and 30.53, runs of 8 30.61).
 __device__ inline int logical_block(const BlockMap& m) {
   const int b = blockIdx.x;
-  if (!m.xcd_remap) return b;
+  if (m.xcd_remap == kXcdNone) return b;
+  if (m.xcd_remap == kXcdRuns) {
+    const int i = b >> 3;
+    return ((i / kXcdRun) * 8 + (b & 7)) * kXcdRun + (i % kXcdRun);
+  }
   const int per = gridDim.x >> 3;
   return (b & 7) * per + (b >> 3);
 }
 
 inline unsigned padded_grid(const BlockMap& m) {
-  if (!m.xcd_remap) return (unsigned)m.count;
-  return (unsigned)(((m.count + 7) / 8) * 8);
+  if (m.xcd_remap == kXcdNone) return (unsigned)m.count;
+  const int unit = m.xcd_remap == kXcdRuns ? 8 * kXcdRun : 8;
+  return (unsigned)((m.count + unit - 1) / unit * unit);
 }
 
 // Wave-wide min / max: DPP exchanges inside 16-lane rows, then the four row results are
@@ -32,16 +41,16 @@ inline unsigned padded_grid(const BlockMap& m) {
 __device__ __forceinline__ int wave_min(int v) {
   v = min(v, lane_xor<1>(v));
   v = min(v, lane_xor<2>(v));
-  v = min(v, lane_xor<4>(v));
-  v = min(v, lane_xor<8>(v));
+  v = min(v, lane_mirror<4>(v));
+  v = min(v, lane_mirror<8>(v));
   return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
              min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 __device__ __forceinline__ int wave_max(int v) {
   v = max(v, lane_xor<1>(v));
   v = max(v, lane_xor<2>(v));
-  v = max(v, lane_xor<4>(v));
-  v = max(v, lane_xor<8>(v));
+  v = max(v, lane_mirror<4>(v));
+  v = max(v, lane_mirror<8>(v));
   return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
              max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
@@ -50,10 +59,20 @@ __device__ __forceinline__ int wave_max(int v) {
 __device__ __forceinline__ unsigned wave_sum(unsigned v) {
   v += (unsigned)lane_xor<1>((int)v);
   v += (unsigned)lane_xor<2>((int)v);
-  v += (unsigned)lane_xor<4>((int)v);
-  v += (unsigned)lane_xor<8>((int)v);
+  v += (unsigned)lane_mirror<4>((int)v);
+  v += (unsigned)lane_mirror<8>((int)v);
   return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
          __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
+}
+
+// Wave-wide OR, uniform across the wave.
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+  v |= (unsigned)lane_xor<1>((int)v);
+  v |= (unsigned)lane_xor<2>((int)v);
+  v |= (unsigned)lane_mirror<4>((int)v);
+  v |= (unsigned)lane_mirror<8>((int)v);
+  return __builtin_amdgcn_readlane(v, 0) | __builtin_amdgcn_readlane(v, 16) |
+         __builtin_amdgcn_readlane(v, 32) | __builtin_amdgcn_readlane(v, 48);
 }
 
 constexpr int kWindow = 4096;   // LDS window entries per block (potential or mass)
@@ -71,8 +90,8 @@ __device__ __forceinline__ unsigned pk_min_u16(unsigned a, unsigned b) {
 __device__ __forceinline__ unsigned wave_min_u16x2(unsigned v) {
   v = pk_min_u16(v, (unsigned)lane_xor<1>((int)v));
   v = pk_min_u16(v, (unsigned)lane_xor<2>((int)v));
-  v = pk_min_u16(v, (unsigned)lane_xor<4>((int)v));
-  v = pk_min_u16(v, (unsigned)lane_xor<8>((int)v));
+  v = pk_min_u16(v, (unsigned)lane_mirror<4>((int)v));
+  v = pk_min_u16(v, (unsigned)lane_mirror<8>((int)v));
   return pk_min_u16(pk_min_u16(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
                     pk_min_u16(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
@@ -138,12 +157,35 @@ struct CellRange {
 
 __device__ __forceinline__ void cells_to_slots(bool in, const int (&j0)[3], unsigned* s) {
   constexpr int kOff = 1 << 14;
+  const int wv = threadIdx.x >> 6;
+  // Cells near those of a lane in the middle of the wave, the usual case: one bit per cell and
+  // axis (12 for x, where a wave of a brick is one lattice layer, 20 for y in one word, 32 for
+  // z in another), two ORs over the lanes, and the extrema from the scalar unit's bit scans.
+  // Three packed minima take three reductions and twice the vector instructions (particle step
+  // of 64 boxes of 64^3 322 us with them, 318 so: memory hides most of it).
+  const int bx = __builtin_amdgcn_readlane(j0[0], 27) - 6;
+  const int by = __builtin_amdgcn_readlane(j0[1], 27) - 10;
+  const int bz = __builtin_amdgcn_readlane(j0[2], 27) - 16;
+  const unsigned dx = (unsigned)(j0[0] - bx), dy = (unsigned)(j0[1] - by);
+  const unsigned dz = (unsigned)(j0[2] - bz);
+  if (__all(in && dx < 12u && dy < 20u && dz < 32u)) {
+    const unsigned mxy = wave_or((1u << dx) | (1u << (dy + 12u))), mz = wave_or(1u << dz);
+    const unsigned mx = mxy & 0xfffu, my = mxy >> 12;
+    const int lx = bx + __builtin_ctz(mx), hx = bx + 31 - __builtin_clz(mx);
+    const int ly = by + __builtin_ctz(my), hy = by + 31 - __builtin_clz(my);
+    const int lz = bz + __builtin_ctz(mz), hz = bz + 31 - __builtin_clz(mz);
+    if ((threadIdx.x & 63) == 0) {
+      s[wv] = (unsigned)(lx + kOff) | ((unsigned)(ly + kOff) << 16);
+      s[kWaves + wv] = (unsigned)(lz + kOff) | ((unsigned)(kOff - hx) << 16);
+      s[2 * kWaves + wv] = (unsigned)(kOff - hy) | ((unsigned)(kOff - hz) << 16);
+    }
+    return;
+  }
   const unsigned none = 0xffffffffu;
   const unsigned p0 = in ? (unsigned)(j0[0] + kOff) | ((unsigned)(j0[1] + kOff) << 16) : none;
   const unsigned p1 = in ? (unsigned)(j0[2] + kOff) | ((unsigned)(kOff - j0[0]) << 16) : none;
   const unsigned p2 = in ? (unsigned)(kOff - j0[1]) | ((unsigned)(kOff - j0[2]) << 16) : none;
   const unsigned r0 = wave_min_u16x2(p0), r1 = wave_min_u16x2(p1), r2 = wave_min_u16x2(p2);
-  const int wv = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
     s[wv] = r0;
     s[kWaves + wv] = r1;

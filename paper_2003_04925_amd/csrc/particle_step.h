@@ -69,24 +69,28 @@ __device__ __forceinline__ long long deposit_block(typename MeshFixed<T>::rho_t*
   WeightT<T> w[8];
   if (in) mesh_weights<T>(f[0], f[1], f[2], w);
   // which of the two corner planes along each axis are interior nodes
-  bool inner[3][2];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    inner[c][0] = j0[c] >= 1 && j0[c] <= n;
-    inner[c][1] = j0[c] >= 0 && j0[c] <= n - 1;
-  }
-  WeightT<T> kept = 0;
-  if (in) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      if (inner[0][(c >> 2) & 1] && inner[1][(c >> 1) & 1] && inner[2][c & 1]) kept += w[c];
-  }
-  long long dropped = active ? (1ll << MeshFixed<T>::bits) - (long long)kept : 0;
+  const auto inner = [&](int c, int k) { return j0[c] + k >= 1 && j0[c] + k <= n; };
+  // the mass each particle drops; a wave whose corners are all interior, the usual case, drops
+  // none and skips the sums
   constexpr bool kBlockDrop = MeshFixed<T>::bits < 32;
+  long long dropped = 0;
+  const bool whole = in && (unsigned)(j0[0] - 1) < (unsigned)(n - 1) &&
+                     (unsigned)(j0[1] - 1) < (unsigned)(n - 1) &&
+                     (unsigned)(j0[2] - 1) < (unsigned)(n - 1);
+  unsigned d = 0;
+  if (!__all(whole)) {
+    WeightT<T> kept = 0;
+    if (in) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (inner(0, (c >> 2) & 1) && inner(1, (c >> 1) & 1) && inner(2, c & 1)) kept += w[c];
+    }
+    dropped = active ? (1ll << MeshFixed<T>::bits) - (long long)kept : 0;
+    if constexpr (kBlockDrop) d = wave_sum((unsigned)dropped);
+  }
   if constexpr (kBlockDrop) {
     // the wave's dropped mass in the slot that block_cells leaves free (read after its
     // barrier): no atomics on the box's counter, whose word all blocks of the box share
-    const unsigned d = wave_sum((unsigned)dropped);
     if ((threadIdx.x & 63) == 0) bounds[3 * kWaves + (threadIdx.x >> 6)] = (int)d;
     dropped = 0;
   }
@@ -170,7 +174,7 @@ __device__ __forceinline__ long long deposit_block(typename MeshFixed<T>::rho_t*
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const int dx = (c >> 2) & 1, dy = (c >> 1) & 1, dz = c & 1;
-      if (inner[0][dx] && inner[1][dy] && inner[2][dz] && w[c] != 0) {
+      if (inner(0, dx) && inner(1, dy) && inner(2, dz) && w[c] != 0) {
         if (use_lds)
           atomicAdd(win + (base + dx * wyz + dy * wz + dz), (W)w[c]);
         else
