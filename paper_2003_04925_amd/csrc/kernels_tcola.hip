@@ -64,9 +64,14 @@ __global__ void __launch_bounds__(kBlock) k_tcola_setup(TcolaArgs<T> a, const do
 }
 
 // The lattice site and array index of this thread: a block is a brick of 4 x 8 x 8 sites, so
-// that its particles share mesh nodes (the arrays are in lattice order: rows of 8 values).
+// that its particles share mesh nodes (the arrays are in lattice order: rows of 8 values).  Each
+// XCD takes a contiguous range of bricks (N >= 16, whose bricks divide evenly): the four bricks
+// that share the arrays' 128-byte lines and the mesh nodes of neighbours then meet in one L2
+// (particle step of 128^3: 100 us with bricks dealt to the XCDs in turn, 67 so).
 __device__ __forceinline__ int64_t tcola_site(int N, int (&idx)[3]) {
-  const int nb = N >> 3, b = blockIdx.x, w = threadIdx.x;
+  const int nb = N >> 3, w = threadIdx.x;
+  int b = blockIdx.x;
+  if ((gridDim.x & 7) == 0) b = (b & 7) * (int)(gridDim.x >> 3) + (b >> 3);
   idx[0] = b / (nb * nb) * 4 + (w >> 6);
   idx[1] = b / nb % nb * 8 + ((w >> 3) & 7);
   idx[2] = b % nb * 8 + (w & 7);
@@ -125,7 +130,7 @@ __device__ __forceinline__ void tcola_force(const T* __restrict__ phi, int N,
 // deposit of the new positions; (kFinalKick) the last half kick and L+.  One LDS window per
 // block serves the potential and then the mass: with one thread per site in lattice order,
 // 32 reads of the potential and 8 atomics per particle in global memory, a step of 128^3
-// particles took 0.35 ms, now 0.10.
+// particles took 0.35 ms, now 0.067.
 template <typename T, int MODE, int NG>
 __global__ void __launch_bounds__(kBlock) k_tcola_particles(TcolaArgs<T> a) {
   __shared__ __align__(16) unsigned long long win[kWindow];
