@@ -16,6 +16,11 @@ namespace scola {
 // logical blocks dealt to the XCDs in turn.
 enum XcdMap : int { kXcdNone = 0, kXcdRanges = 1, kXcdRuns = 2 };
 constexpr int kXcdRun = 4;
+// Runs are for bricks whose particles and meshes (about 64 bytes a particle in FP32) outgrow the
+// 256 MB memory-side cache; within it, ranges keep more of each box in its XCD's L2.  Evolutions
+// of 10 steps, ranges and runs: 3456 bricks 0.516 and 0.573 ms, 8192 0.870 and 0.888, 16000
+// 1.441 and 1.432, 27648 2.117 and 2.098.
+constexpr int kRunBricks = 12288;
 
 struct BlockMap {
   const int* tile = nullptr;

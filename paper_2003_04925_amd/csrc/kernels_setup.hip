@@ -22,7 +22,7 @@ namespace {
 // flight at once; N is a power of two, so the periodic index is a mask).  Bound by memory: 48
 // bytes stored per particle in FP32 and about 40 read.  The stores are streams as large as
 // the evolution's state, so they bypass the caches, where neighbouring bricks find each
-// other's nodes; an XCD takes runs of four of them (kXcdRuns): for the 80 million particles of
+// other's nodes; an XCD takes runs of four of them (kXcdRuns) in large plans: for the 80 million particles of
 // the mixed 256^3 tiling 1.48 ms before, 1.65 with cached stores, 1.57 with single bricks dealt
 // out over the XCDs, 1.17 with a contiguous range for each, 1.12 so.
 template <typename T, int NG>
@@ -261,7 +261,7 @@ void launch_psi(const BoxSetupArgs& a, T* xres, T* pres, hipStream_t s) {
   m.tile = a.blk_tile;
   m.local = a.blk_first;
   m.count = a.n_blocks;
-  if (a.N == a.Np) m.xcd_remap = kXcdRuns;
+  if (a.N == a.Np && a.n_blocks > kRunBricks) m.xcd_remap = kXcdRuns;
   const dim3 grid(padded_grid(m)), block(kBlock);
   if (a.N == a.Np)
     hipLaunchKernelGGL((k_extract_psi<T, NG>), grid, block, 0, s, a.tiles, m, a.phi1, a.phi2,

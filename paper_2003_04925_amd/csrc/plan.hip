@@ -562,13 +562,14 @@ ParticleArgs<T> particle_args(scola_plan* p, void* ws, const StepScalars& sc) {
   return a;
 }
 
-// Block numbering of the particle step: runs where it streams FP32 arrays; FP64 plans, whose
-// 64-bit atomics on the mass mesh cost more away from the box's own L2, take ranges (deposit and
-// solve of 64 boxes of 48^3: 329 us in ranges, 379 in runs).
+// Block numbering of the particle step among `bricks` that are advanced together: runs where it
+// streams FP32 arrays from memory, that is for more than kRunBricks.  FP64 plans, whose 64-bit
+// atomics on the mass mesh cost more away from the box's own L2, take ranges (deposit and solve
+// of 64 boxes of 48^3: 329 us in ranges, 379 in runs).
 template <typename T>
-int particle_map(int remap) {
+int particle_map(int remap, size_t bricks) {
   if (!remap) return kXcdNone;
-  return std::is_same<T, float>::value ? kXcdRuns : kXcdRanges;
+  return std::is_same<T, float>::value && bricks > (size_t)kRunBricks ? kXcdRuns : kXcdRanges;
 }
 
 const scola_class_schedule& sched_of(const scola_plan* p, int M) {
@@ -696,7 +697,7 @@ struct Runner {
       for (size_t c = 0; c < pm.class_M.size(); ++c) {
         BlockMap b = class_group_map(p, pm, c, group, ngroups);
         if (b.count == 0) continue;
-        b.xcd_remap = particle_map<T>(p->sched[c].xcd_remap_particles);
+        b.xcd_remap = particle_map<T>(p->sched[c].xcd_remap_particles, p->part.tile.size());
         hip_check(launch_particles<T>(a, mode, b, p->sched[c].waves_per_simd, s),
                   "particle kernel");
       }
@@ -704,7 +705,7 @@ struct Runner {
       for (int t : tiles) {
         const scola_class_schedule& cs = sched_of(p, p->desc[t].M);
         BlockMap b = tile_map(pm, t);
-        b.xcd_remap = particle_map<T>(cs.xcd_remap_particles);
+        b.xcd_remap = particle_map<T>(cs.xcd_remap_particles, (size_t)b.count);
         hip_check(launch_particles<T>(a, mode, b, cs.waves_per_simd, s), "particle kernel");
       }
     }
@@ -724,7 +725,7 @@ struct Runner {
       for (size_t c = 0; c < pm.class_M.size(); ++c) {
         BlockMap b = class_group_map(p, pm, c, group, ngroups);
         if (b.count == 0) continue;
-        b.xcd_remap = particle_map<T>(p->sched[c].xcd_remap_particles);
+        b.xcd_remap = particle_map<T>(p->sched[c].xcd_remap_particles, p->part.tile.size());
         ParticleArgs<T> a = args_of(scalars(pm.class_tc[c]));
         hip_check(launch_particles<T>(a, mode, b, p->sched[c].waves_per_simd, s),
                   "particle kernel");
@@ -733,7 +734,7 @@ struct Runner {
       for (int t : tiles) {
         const scola_class_schedule& cs = sched_of(p, p->desc[t].M);
         BlockMap b = tile_map(p->part, t);
-        b.xcd_remap = particle_map<T>(cs.xcd_remap_particles);
+        b.xcd_remap = particle_map<T>(cs.xcd_remap_particles, (size_t)b.count);
         ParticleArgs<T> a = args_of(scalars(p->desc[t].tclass));
         hip_check(launch_particles<T>(a, mode, b, cs.waves_per_simd, s), "particle kernel");
       }
@@ -1349,7 +1350,7 @@ void do_tune(scola_plan* p, void* ws, hipStream_t s, int reps) {
     float best = 1e30f;
     for (int remap : {1, 0}) {
       BlockMap b = class_map(pm, c);
-      b.xcd_remap = particle_map<T>(remap);
+      b.xcd_remap = particle_map<T>(remap, p->part.tile.size());
       const float ms = timed([&] {
         hip_check(launch_particles<T>(a, kStep, b, 8, s), "tuning launch");
       });
