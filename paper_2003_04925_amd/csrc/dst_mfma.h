@@ -221,7 +221,8 @@ __device__ __forceinline__ void load_plane(const float* __restrict__ src,
 // 64^3: pencils 36.7 -> 33.7 us, first pass 55.2 -> 53.4, reverse 32.2 -> 28.7); above, the
 // stores, whose rows start off 64-byte boundaries, cost more than that (96^3, 512 boxes:
 // pencils 965 -> 1068 us, first pass 1324 -> 1457).  The third pass stays in LDS at all sizes
-// (64^3 52.4 -> 54.7, 96^3 1080 -> 1183).
+// (64^3 52.4 -> 54.7, 96^3 1080 -> 1183), and so does the persistent step, whose grid barrier
+// waits for the stores (20 steps of 64 boxes of 64^3: 30.9 -> 32.8 ms).
 constexpr bool direct_stores(int R) { return R <= 4; }
 
 // Unnormalised DST-I along z (rows, stride 1) and y (stride n) of the n x n plane held in v;
@@ -313,8 +314,8 @@ __device__ __forceinline__ void plane_dst_mfma(const float (&v)[plane_regs<R, NT
 // pencil p0) of the box's work array, where the chunk's nodes of one x plane are C
 // consecutive words; smem holds the block-maximum slots (mfma_head), the eigenvalues (M
 // floats), then the split lines of the C columns, which the output tile (n rows of C + 1
-// floats) of boxes without direct stores later overwrites.
-template <int R, int NT>
+// floats) later overwrites unless the result is stored DIRECT.
+template <int R, int NT, bool DIRECT>
 __device__ __forceinline__ void pencils_mfma(float* __restrict__ col, int p0, int cw,
                                              const float* __restrict__ eigen,
                                              const _Float16* __restrict__ S,
@@ -391,7 +392,7 @@ __device__ __forceinline__ void pencils_mfma(float* __restrict__ col, int p0, in
   // inverse along x
   sine_times_lines<R, LT, NT>(s, bh, bl, d);
   const float inv = 1.0f / (s1 * s2);
-  if constexpr (direct_stores(R)) {
+  if constexpr (DIRECT) {
     float* const o = col + (int64_t)(16 * w + 4 * (l >> 4)) * n * n + (l & 15);
 #pragma unroll
     for (int tw = 0; tw < D::TW; ++tw)

@@ -93,7 +93,7 @@ k_step_persistent(ParticleArgs<T> pa, MeshArgs<T> ma, BlockMap mp, BlockMap m1, 
     const Sweep w(m1);
     for (int k = w.first; k < w.end; k += w.step) {
       const int L = w.logical(k);
-      if (L < m1.count) poisson_p1_block<T, R, false>(ma, m1, L, smem);
+      if (L < m1.count) poisson_p1_block<T, R, false, 1, kBlock, false>(ma, m1, L, smem);
       __syncthreads();
     }
   }
@@ -102,7 +102,7 @@ k_step_persistent(ParticleArgs<T> pa, MeshArgs<T> ma, BlockMap mp, BlockMap m1, 
     const Sweep w(m2);
     for (int k = w.first; k < w.end; k += w.step) {
       const int L = w.logical(k);
-      if (L < m2.count) poisson_p2_block<T, R>(ma, m2, L, smem);
+      if (L < m2.count) poisson_p2_block<T, R, kBlock, false>(ma, m2, L, smem);
       __syncthreads();
     }
   }

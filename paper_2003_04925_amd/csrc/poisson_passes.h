@@ -598,7 +598,7 @@ __host__ __device__ constexpr size_t plane_region_elems() {
 // NG: ghost layers of the finite-difference order 2 NG (Sec. 3): the box's Phi_BC^0 and
 // potential live on the padded nodes [-NG, M + NG]^3 (padded index = node + NG), and
 // Phi_BCs occupies the NG layers outside the interior on each side.
-template <typename T, int R, bool ADJ, int NG = 1, int NT = kBlock>
+template <typename T, int R, bool ADJ, int NG = 1, int NT = kBlock, bool DIRECT = direct_stores(R)>
 __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const BlockMap& m, int L,
                                                  unsigned char* smem) {
   static_assert(!ADJ || NG == 1, "the reverse passes exist for order 2 only");
@@ -816,7 +816,7 @@ __device__ __forceinline__ void poisson_p1_block(const MeshArgs<T>& a, const Blo
   // mass on, as in the third pass, it was slower (64^3 56 -> 58 us, 112^3 216 -> 251 us)
   if constexpr (!ADJ && kMfma) load_plane<R, NT>(plane, pv.v);
   T* const wk = a.work + base;
-  if constexpr (kMfma && direct_stores(R)) {
+  if constexpr (kMfma && DIRECT) {
     plane_dst_mfma<R, NT, false>(pv.v, wk, reinterpret_cast<_Float16*>(plane),
                                  reinterpret_cast<float*>(smem), op.s);
   } else {
@@ -851,7 +851,7 @@ __device__ __forceinline__ void pencil_solve(T* tile, int cw, int p0, const T* e
   __syncthreads();
 }
 
-template <typename T, int R, int NT = kBlock>
+template <typename T, int R, int NT = kBlock, bool DIRECT = direct_stores(R)>
 __device__ __forceinline__ void poisson_p2_block(const MeshArgs<T>& a, const BlockMap& m, int L,
                                                  unsigned char* smem) {
   const int b = m.base + L;
@@ -862,7 +862,7 @@ __device__ __forceinline__ void poisson_p2_block(const MeshArgs<T>& a, const Blo
   // chunk's nodes of one x plane are C consecutive words
   const int p0 = m.local[b] * C, cw = min(C, n * n - p0);
   if constexpr (std::is_same<T, float>::value) {
-    pencils_mfma<R, NT>(a.work + t.g_off + p0, p0, cw, a.eigen + t.ev_off,
+    pencils_mfma<R, NT, DIRECT>(a.work + t.g_off + p0, p0, cw, a.eigen + t.ev_off,
                     reinterpret_cast<const _Float16*>(a.sine) + t.dm_off, smem);
     return;
   }
