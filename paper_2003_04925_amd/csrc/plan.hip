@@ -1098,13 +1098,17 @@ void do_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws, hipStream
     // the last force's potential also where the operator-level calls look for it
     const T* const src = SegmentRing<T>(p, ws).ph(n - 1);
     T* const dst = reinterpret_cast<T*>(ws_ptr(ws, p->lay.phi));
-    for (int t : tiles) {
-      const size_t Mp = (size_t)p->desc[t].M + 1 + 2 * p->ng;
-      if (tiles.size() == p->desc.size() && t) break;
-      const size_t o = tiles.size() == p->desc.size() ? 0 : (size_t)p->desc[t].h_off;
-      const size_t cnt = tiles.size() == p->desc.size() ? (size_t)p->H : Mp * Mp * Mp;
-      hip_check(hipMemcpyAsync(dst + o, src + o, cnt * sizeof(T), hipMemcpyDeviceToDevice, s),
-                "potential copy");
+    auto copy = [&](size_t first, size_t count) {
+      hip_check(hipMemcpyAsync(dst + first, src + first, count * sizeof(T),
+                               hipMemcpyDeviceToDevice, s), "potential copy");
+    };
+    if (tiles.size() == p->desc.size()) {   // every tile, listed in whichever order
+      copy(0, (size_t)p->H);
+    } else {
+      for (int t : tiles) {
+        const size_t Mp = (size_t)p->desc[t].M + 1 + 2 * p->ng;
+        copy((size_t)p->desc[t].h_off, Mp * Mp * Mp);
+      }
     }
   }
 }

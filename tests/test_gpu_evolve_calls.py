@@ -1,0 +1,41 @@
+"""scola_evolve called in other ways than once over all tiles in order."""
+import pytest
+
+import synthetic
+
+pytestmark = pytest.mark.gpu
+
+NP, L = 32, 100.0
+
+
+def _noise(Np, seed):
+    import torch
+    return torch.from_numpy(synthetic.white_noise(Np, seed)).cuda()
+
+
+@pytest.mark.parametrize("schedule", ["batched", "per_tile"])
+@pytest.mark.parametrize("order", [[5, 2, 7, 0, 1, 3, 6, 4], [0, 7, 6, 5, 4, 3, 2, 1], [3, 1], None])
+def test_last_potential_for_any_tile_order(schedule, order):
+    """A plan with checkpoints leaves the last force's potential of every evolved tile where the
+    operator-level calls look for it, in whichever order the tiles are listed."""
+    import torch
+
+    import paper_2003_04925_amd as S
+    tiles = S.uniform_tiling(NP, 2, 8)
+    w = _noise(NP, 3)
+    plain = S.Simulation(L, NP, tiles, 5, precision="fp64", schedule=schedule)
+    plain.setup(w)
+    plain.evolve()
+    sim = S.Simulation(L, NP, tiles, 5, precision="fp64", schedule=schedule, checkpoint_every=2)
+    sim.setup(w)
+    for _ in range(3):                 # eager, then a recorded graph where one is taken
+        sim.view("phi").fill_(float("nan"))
+        sim.evolve(order)
+        for t, (po, M, go, ho) in enumerate(sim.box_slices()):
+            got, n = sim.view("phi")[ho:ho + (M + 3) ** 3], M ** 3
+            if order is None or t in order:
+                assert torch.equal(got, plain.view("phi")[ho:ho + (M + 3) ** 3]), t
+                for k in ("x_res", "p_res"):
+                    assert torch.equal(sim.view(k)[:, po:po + n], plain.view(k)[:, po:po + n])
+            else:
+                assert bool(got.isnan().all()), t
