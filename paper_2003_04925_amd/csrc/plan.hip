@@ -1080,10 +1080,12 @@ void do_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws, hipStream
     // particle blocks and 47 planes on 256 CUs, 8 to 14 us a kernel whatever its size), so the
     // tiles, which share no data, go out over four streams, each to the one with the fewest
     // particles so far (8 boxes of 48^3, 10 FP64 steps: 3.6 ms one after the other, now
-    // 1.3 with the launches recorded as one graph).  Callers that forbid plan-owned streams get one, and so does a capture that would
-    // have to create them.
+    // 1.3 with the launches recorded as one graph).  Callers that forbid plan-owned streams get
+    // one, and so does a caller's own capture: it would hold the plan's streams until it ends,
+    // and an eager call on another stream would find them captured.
     int S = allow_groups ? std::min<int>(4, (int)tiles.size()) : 1;
-    if (S > 1 && !p->ev_join[S - 2] && capturing(s)) S = 1;
+    const bool own_capture = p->capture_stream && s == p->capture_stream;
+    if (S > 1 && !own_capture && capturing(s)) S = 1;
     std::vector<int64_t> load(S, 0);
     if (S > 1) fork_streams(p, S, s);
     for (int t : tiles) {

@@ -1,4 +1,5 @@
-"""scola_evolve called in other ways than once over all tiles in order."""
+"""scola_evolve called in other ways than once over all tiles in order: tile lists in any order,
+and eager calls while the caller records a graph."""
 import pytest
 
 import synthetic
@@ -39,3 +40,36 @@ def test_last_potential_for_any_tile_order(schedule, order):
                     assert torch.equal(sim.view(k)[:, po:po + n], plain.view(k)[:, po:po + n])
             else:
                 assert bool(got.isnan().all()), t
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_eager_call_while_the_caller_records_another(graph):
+    """Inside a caller's capture the per-tile schedule stays on the captured stream, so that an
+    eager call on a stream that is not being captured still runs before the capture ends."""
+    import torch
+
+    import paper_2003_04925_amd as S
+    tiles = S.uniform_tiling(NP, 2, 8)
+    w = _noise(NP, 4)
+    ref = S.Simulation(L, NP, tiles, 3, precision="fp64").forward(w)["pos"]
+    sim = S.Simulation(L, NP, tiles, 3, precision="fp64", schedule="per_tile")
+    sim.set_graph(graph)
+    sim.setup(w)
+    for _ in range(3):                 # the plan has its streams and events, and its graph
+        sim.evolve()
+    torch.cuda.synchronize()
+    pos = torch.empty_like(ref)
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(g, capture_error_mode="thread_local"):
+        sim.evolve()
+        with torch.cuda.stream(side):
+            sim.evolve([1, 2, 4, 7])
+            sim.evolve()
+            sim.output(pos=pos)
+    torch.cuda.synchronize()
+    assert torch.equal(pos, ref)
+    for _ in range(3):
+        sim.view("x_res").zero_()
+        g.replay()
+        sim.output(pos=pos)
+        assert torch.equal(pos, ref)
