@@ -113,8 +113,8 @@ struct scola_plan {
   hipStream_t aux_stream[3] = {nullptr, nullptr, nullptr};
   hipEvent_t ev_fork = nullptr, ev_join[3] = {nullptr, nullptr, nullptr};
   uint64_t sched_version = 0;         // bumped whenever the schedule changes
-  // the batched evolution over all tiles, captured once per workspace and schedule (from
-  // the second call on) and replayed as one hipGraph launch
+  // the evolution over all tiles, captured once per workspace and schedule (from the second
+  // call on) and replayed as one hipGraph launch
   bool use_graph = true;
   hipStream_t capture_stream = nullptr;
   hipGraph_t evolve_graph = nullptr;
@@ -1079,10 +1079,10 @@ void do_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws, hipStream
     // plain per-tile schedule: launches of one tile each.  They are small (a 48^3 box is 432
     // particle blocks and 47 planes on 256 CUs, 8 to 14 us a kernel whatever its size), so the
     // tiles, which share no data, go out over four streams, each to the one with the fewest
-    // particles so far (8 boxes of 48^3, 10 FP64 steps: 3.6 ms one after the other, now
-    // 1.3 with the launches recorded as one graph).  Callers that forbid plan-owned streams get
-    // one, and so does a caller's own capture: it would hold the plan's streams until it ends,
-    // and an eager call on another stream would find them captured.
+    // particles so far (8 boxes of 48^3, 10 FP64 steps: 3.5 ms one after the other, now 1.2).
+    // Callers that forbid plan-owned streams get one, and so does a caller's own capture: it
+    // would hold the plan's streams until it ends, and an eager call on another stream would
+    // find them captured.
     int S = allow_groups ? std::min<int>(4, (int)tiles.size()) : 1;
     const bool own_capture = p->capture_stream && s == p->capture_stream;
     if (S > 1 && !own_capture && capturing(s)) S = 1;
@@ -1282,6 +1282,23 @@ void do_backward(scola_plan* p, const T* lam_dens, double* grad_w, void* ws, hip
   hip_check(launch_adj_white_noise(sa, lam_phi1, grad_w, s), "adjoint IC filter");
 }
 
+// Launches of an evolution of every tile by itself: L- and the steps, the final kick, and three
+// Poisson passes per force.
+int64_t per_tile_launches(const scola_plan* p) {
+  const int64_t n = p->cfg.n_steps, last = p->cfg.want_momenta ? 1 : 0;
+  return (int64_t)p->desc.size() * (1 + n + last + 3 * (n + last));
+}
+
+// The per-tile schedule is recorded up to this many launches.  A graph of four branches costs
+// the runtime more per node than the launches themselves on four streams, which run while the
+// host goes on; what it saves is the host's part of a short call.  Recorded and eager, ms per
+// call in a row and (waited for): 1 box of 16^3, 97 launches, 0.47 and 0.53 (0.48, 0.54);
+// 8 of 32^3, 136, 0.45 and 0.51 (0.53, 0.56); 8 of 48^3 in FP64, 264, 1.01 and 1.01 (1.40,
+// 1.27); 8 of 32^3 in FP64, 776, 1.93 and 2.01 (2.95, 2.52); 64 of 32^3 in FP64, 576, 1.90 and
+// 1.80 (2.38, 1.85), 1088, 3.77 and 3.27 (4.69, 3.29); 64 of 64^3, 5120, 20.3 and 18.6 (27.2,
+// 19.4); 512 of 16^3, 61440, 314 and 227, after a recording of 390 ms.
+constexpr int64_t kPerTileGraphLaunches = 512;
+
 void drop_graph(scola_plan* p) {
   if (p->evolve_exec) hipGraphExecDestroy(p->evolve_exec);
   if (p->evolve_graph) hipGraphDestroy(p->evolve_graph);
@@ -1291,8 +1308,8 @@ void drop_graph(scola_plan* p) {
   p->graph_eager_calls = 0;
 }
 
-// Record the batched evolution (every kernel, checkpoint copy and counter reset of
-// do_evolve; no memset nodes) on the plan's capture stream and instantiate it.
+// Record the evolution over all tiles (every launch and copy of do_evolve; no memset nodes) on
+// the plan's capture stream and instantiate it.
 template <typename T>
 void capture_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws) {
   if (!p->capture_stream)
@@ -1758,8 +1775,10 @@ scola_status scola_evolve(scola_plan* p, const int32_t* subset, int32_t n_subset
     const std::vector<int> tiles = subset_list(p, subset, n_subset);
     p->forward_ws = (p->cfg.checkpoint_every > 0 && tiles.size() == p->desc.size()) ? ws : nullptr;
     // the per-tile schedule goes eagerly into a caller's own capture, as plain launches
-    const bool graphable = p->use_graph && !p->persistent && tiles.size() == p->desc.size() &&
-                           (p->cfg.schedule == SCOLA_BATCHED || !capturing(s));
+    const bool graphable =
+        p->use_graph && !p->persistent && tiles.size() == p->desc.size() &&
+        (p->cfg.schedule == SCOLA_BATCHED ||
+         (per_tile_launches(p) <= kPerTileGraphLaunches && !capturing(s)));
     if (graphable) {
       if (p->graph_ws != ws || p->graph_version != p->sched_version) {
         drop_graph(p);

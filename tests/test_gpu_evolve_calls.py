@@ -1,5 +1,6 @@
 """scola_evolve called in other ways than once over all tiles in order: tile lists in any order,
-and eager calls while the caller records a graph."""
+eager calls while the caller records a graph, and per-tile plans on either side of the number of
+launches up to which they are recorded."""
 import pytest
 
 import synthetic
@@ -73,3 +74,30 @@ def test_eager_call_while_the_caller_records_another(graph):
         g.replay()
         sim.output(pos=pos)
         assert torch.equal(pos, ref)
+
+
+@pytest.mark.parametrize("Np,per_side,steps,momenta,recorded", [
+    (32, 2, 4, False, True), (32, 2, 15, False, True), (32, 2, 16, False, False),
+    (32, 2, 14, True, True), (32, 2, 15, True, False), (64, 4, 4, False, False)])
+def test_per_tile_recording_is_bounded(Np, per_side, steps, momenta, recorded):
+    """At most 512 launches of the per-tile schedule become a graph (8 tiles: 15 steps, 14 with
+    momenta); plans beyond, which a graph slows down, launch their kernels on every call."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    import paper_2003_04925_amd as S
+    tiles, w = S.uniform_tiling(Np, per_side, 8), _noise(Np, 5)
+    ref = S.Simulation(4.0 * Np, Np, tiles, steps, want_momenta=momenta).forward(w)["pos"]
+    sim = S.Simulation(4.0 * Np, Np, tiles, steps, want_momenta=momenta, schedule="per_tile")
+    sim.setup(w)
+    for _ in range(2):
+        sim.evolve()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        sim.evolve()
+        torch.cuda.synchronize()
+    graphs = sum(e.name == "hipGraphLaunch" for e in prof.events())
+    assert graphs == (1 if recorded else 0)
+    pos = torch.empty_like(ref)
+    sim.output(pos=pos)
+    assert torch.equal(pos, ref)
