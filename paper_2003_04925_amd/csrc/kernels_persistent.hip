@@ -84,7 +84,7 @@ k_step_persistent(ParticleArgs<T> pa, MeshArgs<T> ma, BlockMap mp, BlockMap m1, 
     const Sweep w(mp);
     for (int k = w.first; k < w.end; k += w.step) {
       const int L = w.logical(k);
-      if (L < mp.count) particles_block<T, kStep>(pa, mp, L);
+      if (L < mp.count) particles_block<T, kStep, 1, true>(pa, mp, L);
       __syncthreads();   // the block's LDS is reused by its next logical block
     }
   }

@@ -53,9 +53,12 @@ __device__ inline bool deposit_footprint(int M, double ux, double uy, double uz,
 // particle drops is one unit minus what it keeps (the eight weights sum to exactly one
 // unit).  FP32 plans store the block's total (at most 256 x 2^21 units) in word 3 of
 // hint_out, for the Poisson pass that consumes this deposit to fold into the box's counter,
-// and return 0; FP64 plans store 0 there and return this thread's dropped mass.  Must be
-// called by all threads of the block.
-template <typename T>
+// and return 0; FP64 plans store 0 there and return this thread's dropped mass.  SKIP: a wave
+// that drops nothing skips the sums of what it keeps (fewer vector instructions, 1 % of the
+// particle step; in the persistent step, whose few waves wait for one another, the branch costs
+// more: 20.2 ms for 10 steps of one box of 128^3 with it, 19.1 without).  Must be called by all
+// threads of the block.
+template <typename T, bool SKIP = true>
 __device__ __forceinline__ long long deposit_block(typename MeshFixed<T>::rho_t* __restrict__ rho, int M,
                                           bool active, double ux, double uy, double uz,
                                           typename MeshFixed<T>::window_t* win, int* bounds,
@@ -71,14 +74,14 @@ __device__ __forceinline__ long long deposit_block(typename MeshFixed<T>::rho_t*
   // which of the two corner planes along each axis are interior nodes
   const auto inner = [&](int c, int k) { return j0[c] + k >= 1 && j0[c] + k <= n; };
   // the mass each particle drops; a wave whose corners are all interior, the usual case, drops
-  // none and skips the sums
+  // none
   constexpr bool kBlockDrop = MeshFixed<T>::bits < 32;
   long long dropped = 0;
-  const bool whole = in && (unsigned)(j0[0] - 1) < (unsigned)(n - 1) &&
+  const bool whole = SKIP && in && (unsigned)(j0[0] - 1) < (unsigned)(n - 1) &&
                      (unsigned)(j0[1] - 1) < (unsigned)(n - 1) &&
                      (unsigned)(j0[2] - 1) < (unsigned)(n - 1);
   unsigned d = 0;
-  if (!__all(whole)) {
+  if (!SKIP || !__all(whole)) {
     WeightT<T> kept = 0;
     if (in) {
 #pragma unroll
@@ -588,9 +591,11 @@ __device__ __forceinline__ void block_force_wide(const T* __restrict__ phi, int 
   __syncthreads();   // every thread is done with `bounds` and the window before reuse
 }
 
-// The fused particle step of logical block L (< m.count): called by k_particles below and by
-// the persistent step kernel.
-template <typename T, int MODE, int NG = 1>
+// The fused particle step of logical block L (< m.count): called by k_particles and, with
+// PERSISTENT, by the persistent step kernel, where the momenta are read where they are written
+// (a.pin = a.pres): the three further stream addresses cost that kernel, which spills scalar
+// registers, 2 % (20 steps of 64 boxes of 64^3: 30.7 ms with them, 29.95 without).
+template <typename T, int MODE, int NG = 1, bool PERSISTENT = false>
 __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const BlockMap& m,
                                                 int L) {
   const int b = m.base + L;
@@ -678,7 +683,8 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
   if (kForce) {
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      pr[c] = fresh ? T(0) : __builtin_nontemporal_load(a.pin + (c * P + p0) + tid);
+      pr[c] = fresh ? T(0)
+                    : __builtin_nontemporal_load((PERSISTENT ? ppr[c] : a.pin + (c * P + p0)) + tid);
     // the LPT terms of the kick and of the next position are formed before the force, so
     // Psi1 and Psi2 are not held across it
     const double d2 = sc.D2 - sc.D1 * sc.D1;
@@ -718,8 +724,9 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
   }
   if constexpr (MeshFixed<T>::bits < 32) {
     // FP32: the block's dropped mass travels in its hint (folded by the Poisson pass)
-    deposit_block<T>(a.rho + t.g_off, M, true, u[0], u[1], u[2],
-                     reinterpret_cast<typename MeshFixed<T>::window_t*>(win), bounds, hint);
+    deposit_block<T, !PERSISTENT>(a.rho + t.g_off, M, true, u[0], u[1], u[2],
+                                  reinterpret_cast<typename MeshFixed<T>::window_t*>(win), bounds,
+                                  hint);
   } else {
     __shared__ unsigned long long block_drop;
     if (threadIdx.x == 0) block_drop = 0ull;

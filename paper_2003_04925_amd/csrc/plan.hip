@@ -970,7 +970,7 @@ void zero_node_ranges(const scola_plan* p, const std::vector<int>& tiles, T* arr
 }
 
 // One KDK step k of every class as one persistent launch per class (FP32 batched plans):
-// the particle step and the Poisson passes of force k + 1.
+// the particle step and the Poisson passes of force k + 1.  The momenta are advanced in place.
 template <typename T>
 void persistent_step(const Runner<T>& r, int k, bool fresh, T* next_phi) {
   scola_plan* const p = r.p;
@@ -1031,20 +1031,27 @@ void do_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws, hipStream
     const SegmentRing<T> ring(p, ws);
     const int last = ck > 0 ? (n - 1) / ck * ck : n;      // first step of the last segment
     auto saved = [&](int k) { return ck > 0 && k % ck == 0 && k < n; };
+    // the persistent step advances the momenta in place: its plans copy them to a checkpoint
+    const bool fused = p->persistent && b && G == 1 && !ov_delta && !ov_phi;
     auto at = [&](int k) {                                 // step k reads ...
       r.x_in = saved(k) || (k > last && k < n) ? ring.xs(k) : x;
-      r.p_in = saved(k) ? ring.saved_p(k) : mom;
+      r.p_in = saved(k) && !fused ? ring.saved_p(k) : mom;
       r.phi = k >= last && k < n ? ring.ph(k) : nullptr;
     };
     auto to = [&](int k) {                                 // ... and leaves step k's state
       r.x_out = saved(k) || (k > last && k < n) ? ring.xs(k) : x;
-      r.p_out = saved(k) ? ring.saved_p(k) : mom;
+      r.p_out = saved(k) && !fused ? ring.saved_p(k) : mom;
+    };
+    auto copy_saved_p = [&](int k) {
+      if (fused && saved(k))
+        hip_check(hipMemcpyAsync(ring.saved_p(k), mom, (size_t)3 * p->P * sizeof(T),
+                                 hipMemcpyDeviceToDevice, s), "checkpoint copy");
     };
     at(0);
     to(0);
     r.particles_step(kInit, 0);             // L-: x_res = p_res = 0, deposit x_LPT(t_0)
     r.poisson_step(0);
-    const bool fused = p->persistent && b && G == 1 && !ov_delta && !ov_phi;
+    copy_saved_p(0);
     for (int k = 0; k < n; ++k) {
       at(k);
       to(k + 1);
@@ -1053,6 +1060,7 @@ void do_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws, hipStream
         T* const next = k + 1 >= last && k + 1 < n ? ring.ph(k + 1) : nullptr;
         persistent_step<T>(r, k, r.fresh_start && k == 0, next);
         r.force++;
+        copy_saved_p(k + 1);
         continue;
       }
       r.particles_step(need_force ? kStep : kStepNoDeposit, k);

@@ -1,6 +1,6 @@
 """scola_evolve called in other ways than once over all tiles in order: tile lists in any order,
-eager calls while the caller records a graph, and per-tile plans on either side of the number of
-launches up to which they are recorded."""
+eager calls while the caller records a graph, per-tile plans on either side of the number of
+launches up to which they are recorded, and the persistent step of a plan with checkpoints."""
 import pytest
 
 import synthetic
@@ -101,3 +101,42 @@ def test_per_tile_recording_is_bounded(Np, per_side, steps, momenta, recorded):
     pos = torch.empty_like(ref)
     sim.output(pos=pos)
     assert torch.equal(pos, ref)
+
+
+@pytest.mark.parametrize("every", [1, 2, 7])
+@pytest.mark.parametrize("momenta", [False, True])
+def test_persistent_step_with_checkpoints(every, momenta):
+    """The persistent step leaves the state, the checkpoints and the last segment's positions and
+    potentials, from which the reverse mode starts, bitwise as the default schedule does."""
+    import torch
+
+    import paper_2003_04925_amd as S
+    n = 5
+    w = _noise(NP, 6)
+    sims = []
+    for persistent in (False, True):
+        sim = S.Simulation(L, NP, S.uniform_tiling(NP, 2, 8), n, checkpoint_every=every,
+                           want_momenta=momenta)
+        sim.set_persistent(persistent)
+        sim.set_graph(False)
+        sim.setup(w)
+        sim.evolve()
+        sims.append(sim)
+    a, b = sims
+    assert b.persistent()["enabled"] and b.persistent()["barrier_failures"] == 0
+    for k in ("x_res", "p_res", "phi"):
+        assert torch.equal(a.view(k), b.view(k)), k
+    P, H = a.layout.n_particles, a.layout.n_padded
+
+    def kept(sim, name, first, count):
+        off = sim._ws_off + getattr(sim.layout, name) + 4 * first
+        return sim.workspace[off:off + 4 * count].view(torch.float32)
+    saved = (n + every - 1) // every
+    assert torch.equal(kept(a, "ckpt", 0, saved * 6 * P), kept(b, "ckpt", 0, saved * 6 * P))
+    last = (n - 1) // every * every
+    for k in range(last, n):
+        slot = k % (every + 1)
+        assert torch.equal(kept(a, "seg_phi", slot * H, H), kept(b, "seg_phi", slot * H, H)), k
+        if k > last:
+            assert torch.equal(kept(a, "seg_x", slot * 3 * P, 3 * P),
+                               kept(b, "seg_x", slot * 3 * P, 3 * P)), k
