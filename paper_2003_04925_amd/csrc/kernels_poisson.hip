@@ -50,41 +50,46 @@ constexpr int first_pass_waves() {
 
 // Threads of a block.  The FP32 passes above 64^3 have more 16-row tiles of the sine matrix than
 // a block of 256 has waves: with 512, each wave has one tile, half the values in flight per
-// thread and so fewer registers, and more waves fit a CU (512 boxes of 96^3: first pass 1362 ->
-// 1324 us, pencils 1109 -> 965, third 1042 -> 1080; 29 of 112^3: 222 -> 163, 121 -> 107, 167 ->
-// 128; 80^3: 138 -> 125, 99 -> 85, 114 -> 99).  64 R threads, where no wave is idle in the
-// products, were slower (96^3: 1522, 1049 and 1244 us): six or seven waves do not spread evenly
-// over the four SIMDs.
-template <typename T, int R>
+// thread and so fewer registers, and more waves fit a CU.  With 256 and 512 threads, us for 64
+// boxes: first pass of 96^3 228 and 195, of 112^3 455 and 347, of 128^3 577 and 462; pencils of
+// 80^3 107 and 95, 96^3 159 and 141, 112^3 256 and 235; third pass of 80^3 105 and 106, 112^3 337
+// and 276, 128^3 453 and 367; reverse third pass of 80^3 to 128^3 146, 222, 411, 539 and 129,
+// 197, 324, 481.  The third pass of 96^3, whose six tiles leave two of eight waves idle in the
+// products, takes the same time either way (64 boxes 159 and 153, 512 boxes 1046 and 1059).  The
+// pencils of 128^3, whose eight tiles four waves share evenly, are faster with 256 (367 and 393).
+// 64 R threads, where no wave is idle, were slower (96^3, 512 boxes: 1522, 1049 and 1244): six or
+// seven waves do not spread evenly over the four SIMDs.
+template <typename T, int R, int PASS>
 constexpr int pass_threads() {
-  return std::is_same<T, float>::value && R >= 5 ? 512 : kBlock;
+  if (!std::is_same<T, float>::value || R < 5) return kBlock;
+  return PASS == 2 && R == 8 ? kBlock : 512;
 }
 
 template <typename T, int R, bool ADJ, int NG>
-__global__ void __launch_bounds__((pass_threads<T, R>()))
+__global__ void __launch_bounds__((pass_threads<T, R, 1>()))
 __attribute__((amdgpu_waves_per_eu(first_pass_waves<T, R, ADJ, NG>())))
 k_poisson_p1(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p1_block<T, R, ADJ, NG, pass_threads<T, R>()>(a, m, L, smem);
+  if (L < m.count) poisson_p1_block<T, R, ADJ, NG, pass_threads<T, R, 1>()>(a, m, L, smem);
 }
 
 template <typename T, int R>
-__global__ void __launch_bounds__((pass_threads<T, R>()))
+__global__ void __launch_bounds__((pass_threads<T, R, 2>()))
 __attribute__((amdgpu_waves_per_eu(pass_waves<T, R>())))
 k_poisson_p2(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p2_block<T, R, pass_threads<T, R>()>(a, m, L, smem);
+  if (L < m.count) poisson_p2_block<T, R, pass_threads<T, R, 2>()>(a, m, L, smem);
 }
 
 template <typename T, int R, bool ADJ, int NG>
-__global__ void __launch_bounds__((pass_threads<T, R>()))
+__global__ void __launch_bounds__((pass_threads<T, R, 3>()))
 __attribute__((amdgpu_waves_per_eu(pass_waves<T, R, ADJ, NG>())))
 k_poisson_p3(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p3_block<T, R, ADJ, NG, pass_threads<T, R>()>(a, m, L, smem);
+  if (L < m.count) poisson_p3_block<T, R, ADJ, NG, pass_threads<T, R, 3>()>(a, m, L, smem);
 }
 
 }  // namespace
@@ -107,7 +112,7 @@ size_t poisson_lds_bytes(int M, int pass, int ng) {
     // split lines that alias it); P2: the eigenvalues, then the split lines of the chunk's
     // columns aliased by the output tile
     const int R = M / 16;
-    const size_t head = R >= 5 ? mfma_head<512>() : mfma_head<kBlock>();
+    const size_t head = R >= 5 ? mfma_head<512>() : mfma_head<kBlock>();   // of any block size
     const size_t region = std::max(n * n * sizeof(float), mfma_split_bytes(R));
     if (pass == 1 || pass == 3) return head + region;
     const size_t lines =
@@ -148,15 +153,15 @@ hipError_t launch_poisson_R(const MeshArgs<T>& a, const BlockMap& p1, const Bloc
       done.fetch_or(bit);
     }
   }
-  const dim3 block(pass_threads<T, R>());
   if (p1.count > 0)
-    hipLaunchKernelGGL((k_poisson_p1<T, R, ADJ, NG>), dim3(padded_grid(p1)), block, l1, s,
-                       a, p1);
+    hipLaunchKernelGGL((k_poisson_p1<T, R, ADJ, NG>), dim3(padded_grid(p1)),
+                       dim3(pass_threads<T, R, 1>()), l1, s, a, p1);
   if (p2.count > 0)
-    hipLaunchKernelGGL((k_poisson_p2<T, R>), dim3(padded_grid(p2)), block, l2, s, a, p2);
+    hipLaunchKernelGGL((k_poisson_p2<T, R>), dim3(padded_grid(p2)),
+                       dim3(pass_threads<T, R, 2>()), l2, s, a, p2);
   if (p3.count > 0)
-    hipLaunchKernelGGL((k_poisson_p3<T, R, ADJ, NG>), dim3(padded_grid(p3)), block, l3, s,
-                       a, p3);
+    hipLaunchKernelGGL((k_poisson_p3<T, R, ADJ, NG>), dim3(padded_grid(p3)),
+                       dim3(pass_threads<T, R, 3>()), l3, s, a, p3);
   return hipGetLastError();
 }
 
