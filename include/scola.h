@@ -116,7 +116,12 @@ typedef struct {
                               kick and L+ (App. B) so momenta are available */
   int32_t checkpoint_every;/* 0: forward only.  c > 0: the forward stores (x_res, p_res)
                               before steps 0, c, 2c, ... and scola_backward is available
-                              (it recomputes each segment of c steps) */
+                              (it recomputes each segment of c steps but the last, whose
+                              states the forward keeps).  FP64 results are the same bits for
+                              every c.  FP32 plans that scola_backward serves (order 2,
+                              N_lpt = N_p, one final time) form phi1 and phi2 by other FP64
+                              transforms when c > 0: they differ in the last bits (2e-15 of
+                              the maximum), and FP32 results within their rounding */
 } scola_config;
 
 typedef struct scola_plan scola_plan;
@@ -236,7 +241,7 @@ scola_status scola_forward_noalloc(scola_plan* plan, const double* d_white_noise
  * (R [N_out^3], device), writes d loss / d white noise (double [N_lpt^3], device).  Needs a
  * plan with checkpoint_every > 0 and a preceding scola_forward over all tiles on the same
  * workspace (else SCOLA_ESTATE).  Segments of checkpoint_every steps are recomputed from
- * the checkpoints, then reversed step by step: transpose of the drift and kick, of the
+ * the checkpoints (the last one is there from the forward), then reversed step by step: transpose of the drift and kick, of the
  * gradient-then-CiC-interpolation chain (one scalar scatter per particle onto the padded
  * nodes), the same Dirichlet DST solve (the FDA-2 Dirichlet Laplacian is symmetric) and of
  * the deposit; finally the FP64 transposes of Phi_BC^0, Psi = D phi, the second-order

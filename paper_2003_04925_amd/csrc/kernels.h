@@ -179,8 +179,8 @@ enum ParticleMode { kDepositOnly = 0, kStep = 1, kStepNoDeposit = 2, kFinalKick 
 // the spectrum and order of `a`.
 hipError_t launch_periodic_tables(void* buf, int N, const SetupArgs& a, PeriodicTables* out,
                                   hipStream_t s);
-// white noise -> phi1, phi2 (A.1, A.2); the radix-2 form (order 2) keeps the rounding that
-// gradients of FP32 plans depend on (kernels_setup_radix2.hip)
+// white noise -> phi1, phi2 (A.1, A.2); the radix-2 form (order 2) keeps the rounding with which
+// FP32 plans have formed their gradients (kernels_setup_radix2.hip)
 hipError_t launch_setup_potentials(const SetupArgs& a, hipStream_t s);
 hipError_t launch_setup_potentials_radix2(const SetupArgs& a, hipStream_t s);
 template <typename T>

@@ -1,11 +1,15 @@
 // Lagrangian potentials by complex radix-2 transforms, for FP32 plans with the reverse mode
-// only (scola_plan decides): the fused transforms of kernels_fft.hip are 4 to 5 times as fast
-// and as accurate, but they round phi differently in the last bit, and in FP32 that moves a
-// few particles across a cell face, where the gradient of the CiC weights has a kink: on
-// 128^3 particles and 20 steps the returned gradient changes by 2.7e-5 of its norm, about its
-// distance from an FP64 run (2.9e-5) and far more than its run-to-run differences (4e-7).
-// With these transforms a gradient stays reproducible to those 4e-7.  They take 0.7 ms of
-// the 39 ms of such a run's forward and reverse pass.
+// only (do_setup decides).  The fused transforms of kernels_fft.hip are 4 to 5 times as fast, as
+// accurate and as reproducible, but they round phi differently in the last bits (1e-15 and 2e-15
+// of the maximum of phi1 and phi2).  Some tens of the FP32 displacements then round the other
+// way, and where such a particle lies on a cell face, at which the gradient of the CiC weights
+// has a kink, the returned gradient changes by more than it does from one run to the next: over
+// 120 noise fields of 64^3 and 128^3 particles and 20 or 24 steps, by up to 1e-6 of its norm and
+// 2.2e-6 of its largest entry, against 4e-7 and 1e-7 between two runs (its distance from an FP64
+// run is 2.9e-5).  Neither is nearer the truth; these transforms keep the gradients of such plans
+// where they were to within their run-to-run differences, for 0.7 ms of the 35 ms of a forward
+// and reverse pass.  A plan without checkpoints takes the fused ones, so that its FP32 results
+// can differ from these in their rounding.
 #include "common.h"
 #include "kernels.h"
 

@@ -859,7 +859,7 @@ template <typename T>
 void do_setup(scola_plan* p, const double* w, void* ws, hipStream_t s) {
   SetupArgs a = setup_args(p, w, ws);
   // where scola_backward can follow in FP32, the rounding of phi decides which side of a cell
-  // face a few particles take (see launch_setup_potentials_radix2)
+  // face a particle takes now and then (see kernels_setup_radix2.hip)
   const bool fp32_reverse = std::is_same<T, float>::value && p->cfg.checkpoint_every > 0 &&
                             p->ng == 1 && p->N_lpt == p->cfg.Np && p->tclasses.size() == 1;
   hip_check(fp32_reverse ? launch_setup_potentials_radix2(a, s) : launch_setup_potentials(a, s),
