@@ -286,9 +286,9 @@ scola_status scola_evolve_overrides(scola_plan* plan, const void* d_delta, const
  *                        (6 = 80 registers, 8 = 64; FP64 plans need more than 64 and run
  *                        at the occupancy their registers allow);
  *   xcd_remap_particles  1: blocks numbered so runs of four neighbouring bricks go to the 8
- *                        XCDs in turn (FP64 plans, and up to 12288 bricks of 256 particles:
- *                        so each XCD takes a contiguous run of whole boxes); 0: hardware
- *                        order;
+ *                        XCDs in turn (FP64 plans, up to 12288 bricks of 256 particles, and
+ *                        launches of one tile: so each XCD takes a contiguous run of blocks);
+ *                        0: hardware order;
  *   xcd_remap_mesh       1: blocks of the three Poisson passes numbered so each XCD takes a
  *                        contiguous run of whole boxes (their meshes stay in one L2).
  * Defaults {8, 1, 1}.  scola_plan_tune times the choices per class on the workspace's

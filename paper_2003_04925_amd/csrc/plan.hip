@@ -562,8 +562,9 @@ ParticleArgs<T> particle_args(scola_plan* p, void* ws, const StepScalars& sc) {
   return a;
 }
 
-// Block numbering of the particle step among `bricks` that are advanced together: runs where it
-// streams FP32 arrays from memory, that is for more than kRunBricks.  FP64 plans, whose 64-bit
+// Block numbering of the batched particle step among `bricks` that are advanced together: runs
+// where it streams FP32 arrays from memory, that is for more than kRunBricks (launches of one
+// tile, at most 8192 bricks, take ranges).  FP64 plans, whose 64-bit
 // atomics on the mass mesh cost more away from the box's own L2, take ranges (deposit and solve
 // of 64 boxes of 48^3: 329 us in ranges, 379 in runs).
 template <typename T>
@@ -705,7 +706,7 @@ struct Runner {
       for (int t : tiles) {
         const scola_class_schedule& cs = sched_of(p, p->desc[t].M);
         BlockMap b = tile_map(pm, t);
-        b.xcd_remap = particle_map<T>(cs.xcd_remap_particles, (size_t)b.count);
+        b.xcd_remap = cs.xcd_remap_particles ? kXcdRanges : kXcdNone;
         hip_check(launch_particles<T>(a, mode, b, cs.waves_per_simd, s), "particle kernel");
       }
     }
@@ -734,7 +735,7 @@ struct Runner {
       for (int t : tiles) {
         const scola_class_schedule& cs = sched_of(p, p->desc[t].M);
         BlockMap b = tile_map(p->part, t);
-        b.xcd_remap = particle_map<T>(cs.xcd_remap_particles, (size_t)b.count);
+        b.xcd_remap = cs.xcd_remap_particles ? kXcdRanges : kXcdNone;
         ParticleArgs<T> a = args_of(scalars(p->desc[t].tclass));
         hip_check(launch_particles<T>(a, mode, b, cs.waves_per_simd, s), "particle kernel");
       }
