@@ -30,8 +30,7 @@ __device__ inline int wrap(int i, int n) {
 // [outer][n][inner].  Each block transforms `lines` lines staged in LDS with a radix-2
 // Stockham pass per stage.  sign = -1 forward, +1 inverse (unnormalised).
 __global__ void __launch_bounds__(kBlock) k_fft_axis(double2* __restrict__ data, int n,
-                                                      int log2n, int64_t inner, int lines,
-                                                      double sign) {
+                                                      int64_t inner, int lines, double sign) {
   extern __shared__ double2 lds[];
   double2* buf0 = lds;
   double2* buf1 = lds + (size_t)lines * n;
@@ -168,15 +167,13 @@ __global__ void k_second_order_source(const double* __restrict__ phi, double2* _
 inline unsigned grid1(int64_t n, int b = kBlock) { return (unsigned)((n + b - 1) / b); }
 
 hipError_t fft3d(double2* c, int N, double sign, hipStream_t s) {
-  int log2n = 0;
-  while ((1 << log2n) < N) ++log2n;
   const int lines = N >= 1024 ? 1 : 1024 / N;     // 32 KiB of LDS per block
   const size_t lds = (size_t)2 * lines * N * sizeof(double2);
   const int64_t total_lines = (int64_t)N * N;
   const unsigned blocks = (unsigned)((total_lines + lines - 1) / lines);
   const int64_t inners[3] = {(int64_t)N * N, N, 1};   // axes x, y, z
   for (int ax = 0; ax < 3; ++ax) {
-    hipLaunchKernelGGL(k_fft_axis, dim3(blocks), dim3(kBlock), lds, s, c, N, log2n,
+    hipLaunchKernelGGL(k_fft_axis, dim3(blocks), dim3(kBlock), lds, s, c, N,
                        inners[ax], lines, sign);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -36,16 +36,8 @@ inline unsigned padded_grid(const BlockMap& m) {
   return (unsigned)((m.count + unit - 1) / unit * unit);
 }
 
-// Wave-wide min / max: DPP exchanges inside 16-lane rows, then the four row results are
-// read into scalars; the result is uniform across the wave.
-__device__ __forceinline__ int wave_min(int v) {
-  v = min(v, lane_xor<1>(v));
-  v = min(v, lane_xor<2>(v));
-  v = min(v, lane_mirror<4>(v));
-  v = min(v, lane_mirror<8>(v));
-  return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-             min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
+// Wave-wide maximum: DPP exchanges inside 16-lane rows, then the four row results are read into
+// scalars; the result is uniform across the wave.
 __device__ __forceinline__ int wave_max(int v) {
   v = max(v, lane_xor<1>(v));
   v = max(v, lane_xor<2>(v));

@@ -681,15 +681,6 @@ struct Runner {
   // the evolution starts without writing the zeros of L- (no checkpoint reads them)
   bool fresh_start = false;
 
-  std::vector<BlockMap> maps(const Maps& m) const {
-    std::vector<BlockMap> out;
-    if (batched) {
-      out.push_back(full_map(m));
-    } else {
-      for (int t : tiles) out.push_back(tile_map(m, t));
-    }
-    return out;
-  }
   void particles(int mode, const StepScalars& sc) {
     ParticleArgs<T> a = particle_args<T>(p, ws, sc);
     redirect(a);
