@@ -64,18 +64,25 @@ __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
 // B.2: core particles -> global lattice order; with DENSITY the periodic CiC of the core
 // particles on the N_out^3 output grid (nodes at integer multiples of L / N_out).  One block
 // per brick; bricks without core particles leave at once.  Bound by its streams: 36 bytes read
-// and 12 written per core particle in FP32, and the window's flush (512^3 particles: 36.6 ms
-// with eight global atomics per particle, now 4.9).
+// and 12 written per core particle in FP32, by the many short blocks of boxes with wide buffers,
+// and with DENSITY by the window's flush (64 boxes of 64^3: positions 41 us, density 89, 437 with
+// eight global atomics per particle; 64 of 96^3: 213, 545, 3010).
 template <typename T, bool DENSITY>
 __global__ void __launch_bounds__(kBlock) k_output(OutputArgs<T> a, BlockMap m) {
   const int L = logical_block(m);
   if (L >= m.count) return;
   const int b = m.base + L;
-  const TileDesc t = a.tiles[m.tile[b]];
-  const int M = t.M, nb = M >> 3, brick = m.local[b], w = threadIdx.x;
-  const int i0 = brick / (nb * nb) * 4, j0 = brick / nb % nb * 8, k0 = brick % nb * 8;
+  const int ti = m.tile[b], brick = m.local[b], w = threadIdx.x;
+  const TileDesc t = a.tiles[ti];
   const int lo = t.core_lo[0], hi = t.core_lo[0] + t.core_n;
-  if (i0 + 4 <= lo || i0 >= hi || j0 + 8 <= lo || j0 >= hi || k0 + 8 <= lo || k0 >= hi) return;
+  // axis by axis: most blocks of a box with a wide buffer leave after the first division
+  const unsigned nb = (unsigned)t.M >> 3, row = (unsigned)brick / nb;
+  const int i0 = (int)(row / nb) * 4;
+  if (i0 + 4 <= lo || i0 >= hi) return;
+  const int j0 = (int)(row % nb) * 8;
+  if (j0 + 8 <= lo || j0 >= hi) return;
+  const int k0 = (int)((unsigned)brick - row * nb) * 8;
+  if (k0 + 8 <= lo || k0 >= hi) return;
   const int idx[3] = {i0 + (w >> 6), j0 + ((w >> 3) & 7), k0 + (w & 7)};
   const bool core = idx[0] >= lo && idx[0] < hi && idx[1] >= lo && idx[1] < hi && idx[2] >= lo &&
                     idx[2] < hi;
@@ -88,11 +95,17 @@ __global__ void __launch_bounds__(kBlock) k_output(OutputArgs<T> a, BlockMap m) 
                           ((t.origin[1] + idx[1]) & (Np - 1))) * Np +
                          ((t.origin[2] + idx[2]) & (Np - 1));
     const int64_t Np3 = (int64_t)Np * Np * Np;
+    T s1[3], s2[3], xr[3];   // all nine loads in flight at once
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      s1[c] = a.psi1[c * P + p];
+      s2[c] = a.psi2[c * P + p];
+      xr[c] = a.xres[c * P + p];
+    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       // the tile's own final growth factors (tiles may end at different scale factors)
-      const double u = lpt_base(idx[c] + 0.5, t.D1f, a.psi1[c * P + p], t.D2f,
-                                a.psi2[c * P + p]) + (double)a.xres[c * P + p];
+      const double u = lpt_base(idx[c] + 0.5, t.D1f, s1[c], t.D2f, s2[c]) + (double)xr[c];
       ug[c] = t.origin[c] + u;
       if (a.pos) {
         T xl = (T)(wrap_position(ug[c], (double)Np) * a.cell);
