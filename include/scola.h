@@ -338,8 +338,8 @@ scola_status scola_plan_set_graph(scola_plan* plan, int32_t enable);
 /* One persistent launch per KDK step (the batching pattern of a single fused launch per
  * step): with enable != 0, every step of the batched evolution that deposits runs, per
  * class, the fused particle step of all bricks and the three Poisson passes of the next
- * force in ONE cooperative launch whose grid is the number of workgroups resident at once,
- * the phases separated by grid-wide barriers (bounded waits; a cooperative launch fails
+ * force in ONE cooperative launch whose workgroups are all resident at once (one per CU for
+ * classes whose planes fit so, else up to three), the phases separated by grid-wide barriers (bounded waits; a cooperative launch fails
  * rather than oversubscribe, so no wait can deadlock).  Results are bitwise those of the
  * default schedule.  Runs eagerly (no hipGraph) on one box group; FP32 batched plans only
  * (SCOLA_EUNSUPPORTED for FP64, SCOLA_EINVAL for the per-tile schedule).  It is slower than

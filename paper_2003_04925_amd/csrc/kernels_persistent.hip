@@ -2,7 +2,7 @@
 // of every brick, then the three Poisson passes of the next force, separated by grid-wide
 // barriers (the dependencies are per box, but a box's passes need all of its bricks and all
 // of its planes, so a grid barrier between the phases is the simplest sufficient sync).
-// The grid is sized to the number of workgroups that are resident at once (a cooperative
+// The grid is at most the number of workgroups that are resident at once (a cooperative
 // launch fails rather than oversubscribe), every workgroup walks the logical blocks of each
 // phase, and every workgroup reaches every barrier, so no wait can deadlock.  The phases
 // call the same device functions as the separate kernels, so results are bitwise those of
@@ -136,7 +136,15 @@ hipError_t launch_persistent_R(const ParticleArgs<T>& pa, const MeshArgs<T>& ma,
     return e;
   if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlock, lds)) != hipSuccess)
     return e;
-  const int most = std::max(std::max(mp.count, m1.count), std::max(m2.count, m3.count));
+  // Every block takes part in every barrier, whose waits grow with their number, so more blocks
+  // must pay by the work they overlap.  Where a block per CU holds every plane and pencil chunk, a
+  // second one does not (6 steps of one box of 96^3: 2.37 ms with 512 blocks, 1.64 with 256; of
+  // 64^3 3.05 with 1024 and 0.83), and a fourth per CU does not in larger classes (64 boxes of
+  // 48^3 4.96 ms with 1024 and 4.23 with 768, of 64^3 8.43 and 7.34, 512 of 64^3 44.4 and 43.5;
+  // with 512 3.79, 7.25 and 47.1).
+  const int mesh = std::max(m1.count, std::max(m2.count, m3.count));
+  per_cu = std::min(per_cu, mesh <= cus ? 1 : 3);
+  const int most = std::max(mp.count, mesh);
   int grid = std::min(per_cu * cus, ((most + 7) / 8) * 8);
   grid = std::max(8, grid / 8 * 8);
   if (grid > per_cu * cus) return hipErrorCooperativeLaunchTooLarge;

@@ -1,6 +1,7 @@
 """scola_evolve called in other ways than once over all tiles in order: tile lists in any order,
 eager calls while the caller records a graph, per-tile plans on either side of the number of
-launches up to which they are recorded, and the persistent step of a plan with checkpoints."""
+launches up to which they are recorded, the persistent step of a plan with checkpoints, and its
+grid."""
 import pytest
 
 import synthetic
@@ -140,3 +141,29 @@ def test_persistent_step_with_checkpoints(every, momenta):
         if k > last:
             assert torch.equal(kept(a, "seg_x", slot * 3 * P, 3 * P),
                                kept(b, "seg_x", slot * 3 * P, 3 * P)), k
+
+
+@pytest.mark.parametrize("Np,per_side,buffer", [(32, 1, 8), (64, 1, 16), (64, 1, 24), (32, 2, 8),
+                                                (64, 2, 8)])
+def test_persistent_grid(Np, per_side, buffer):
+    """One block per CU where that holds every plane and pencil chunk of the class, else at most
+    three; the state is the default schedule's, bitwise, on either side."""
+    import torch
+
+    import paper_2003_04925_amd as S
+    tiles, w = S.uniform_tiling(Np, per_side, buffer), _noise(Np, 7)
+    sims = []
+    for persistent in (False, True):
+        sim = S.Simulation(4.0 * Np, Np, tiles, 3)
+        sim.set_persistent(persistent)
+        sim.setup(w)
+        sim.evolve()
+        sims.append(sim)
+    for k in ("x_res", "p_res", "phi"):
+        assert torch.equal(sims[0].view(k), sims[1].view(k)), k
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    M = Np // per_side + 2 * buffer
+    mesh = per_side ** 3 * max(M + 3, ((M - 1) ** 2 + 63) // 64)
+    st = sims[1].persistent()
+    assert st["barrier_failures"] == 0
+    assert (st["grid"] <= cus) == (mesh <= cus) and st["grid"] <= 3 * cus
