@@ -341,7 +341,10 @@ scola_status scola_plan_set_graph(scola_plan* plan, int32_t enable);
  * force in ONE cooperative launch whose workgroups are all resident at once (one per CU for
  * classes whose planes fit so, else up to three), the phases separated by grid-wide barriers (bounded waits; a cooperative launch fails
  * rather than oversubscribe, so no wait can deadlock).  Results are bitwise those of the
- * default schedule.  Runs eagerly (no hipGraph) on one box group; FP32 batched plans only
+ * default schedule.  Runs eagerly (no hipGraph) on one box group, and tile subsets on `stream`
+ * alone.  The runtime keeps a hardware queue for cooperative launches from the first one on:
+ * in the same process, box groups and the per-tile schedule's streams of other plans share
+ * the remaining ones and can run slower than on one stream.  FP32 batched plans only
  * (SCOLA_EUNSUPPORTED for FP64, SCOLA_EINVAL for the per-tile schedule).  It is slower than
  * the default (the kernel carries the register and LDS needs of its heaviest phase into all
  * of them), so the default is off.

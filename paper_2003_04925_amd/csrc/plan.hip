@@ -1082,8 +1082,11 @@ void do_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws, hipStream
     // particles so far (8 boxes of 48^3, 10 FP64 steps: 3.5 ms one after the other, now 1.2).
     // Callers that forbid plan-owned streams get one, and so does a caller's own capture: it
     // would hold the plan's streams until it ends, and an eager call on another stream would
-    // find them captured.
-    int S = allow_groups ? std::min<int>(4, (int)tiles.size()) : 1;
+    // find them captured.  Subsets of a plan with the persistent step get one too: cooperative
+    // launches keep a hardware queue of their own, and four more streams then take turns on the
+    // others (4 boxes of 32^3, 6 FP32 steps: 0.64 ms on one stream, 0.90 on four; 0.46 on four
+    // without cooperative launches in the process).
+    int S = allow_groups && !p->persistent ? std::min<int>(4, (int)tiles.size()) : 1;
     const bool own_capture = p->capture_stream && s == p->capture_stream;
     if (S > 1 && !own_capture && capturing(s)) S = 1;
     std::vector<int64_t> load(S, 0);

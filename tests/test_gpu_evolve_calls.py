@@ -167,3 +167,27 @@ def test_persistent_grid(Np, per_side, buffer):
     st = sims[1].persistent()
     assert st["barrier_failures"] == 0
     assert (st["grid"] <= cus) == (mesh <= cus) and st["grid"] <= 3 * cus
+
+
+def test_subsets_of_a_persistent_plan():
+    """Tile subsets of a plan with the persistent step, which run on one stream: the default
+    schedule's bits, in the order of the caller's stream."""
+    import torch
+
+    import paper_2003_04925_amd as S
+    tiles, w = S.uniform_tiling(NP, 2, 8), _noise(NP, 8)
+    sims = [S.Simulation(L, NP, tiles, 3) for _ in range(2)]
+    for sim in sims:
+        sim.setup(w)
+        sim.evolve()
+    a, b = sims
+    b.set_persistent(True)
+    b.evolve()
+    for _ in range(2):
+        for k in ("x_res", "p_res"):
+            b.view(k).fill_(-7.0)
+        b.evolve([6, 0, 3])
+        b.evolve([1, 2, 4, 5, 7])
+        for k in ("x_res", "p_res"):
+            assert torch.equal(a.view(k), b.view(k)), k
+    assert b.persistent()["barrier_failures"] == 0
