@@ -147,20 +147,21 @@ struct CellRange {
   bool any;
 };
 
+template <bool NEAR = true>
 __device__ __forceinline__ void cells_to_slots(bool in, const int (&j0)[3], unsigned* s) {
   constexpr int kOff = 1 << 14;
   const int wv = threadIdx.x >> 6;
   // Cells near those of a lane in the middle of the wave, the usual case: one bit per cell and
   // axis (12 for x, where a wave of a brick is one lattice layer, 20 for y in one word, 32 for
   // z in another), two ORs over the lanes, and the extrema from the scalar unit's bit scans.
-  // Three packed minima take three reductions and twice the vector instructions (particle step
-  // of 64 boxes of 64^3 322 us with them, 318 so: memory hides most of it).
+  // Three packed minima take three reductions and twice the vector instructions (NEAR: see
+  // deposit_block for where that tells).
   const int bx = __builtin_amdgcn_readlane(j0[0], 27) - 6;
   const int by = __builtin_amdgcn_readlane(j0[1], 27) - 10;
   const int bz = __builtin_amdgcn_readlane(j0[2], 27) - 16;
   const unsigned dx = (unsigned)(j0[0] - bx), dy = (unsigned)(j0[1] - by);
   const unsigned dz = (unsigned)(j0[2] - bz);
-  if (__all(in && dx < 12u && dy < 20u && dz < 32u)) {
+  if (NEAR && __all(in && dx < 12u && dy < 20u && dz < 32u)) {
     const unsigned mxy = wave_or((1u << dx) | (1u << (dy + 12u))), mz = wave_or(1u << dz);
     const unsigned mx = mxy & 0xfffu, my = mxy >> 12;
     const int lx = bx + __builtin_ctz(mx), hx = bx + 31 - __builtin_clz(mx);
@@ -212,10 +213,11 @@ __device__ __forceinline__ void cells_from_slots(const unsigned* s, unsigned (&q
 }
 
 // q receives the packed words of the extent, the form in which it is kept between launches.
+template <bool NEAR = true>
 __device__ __forceinline__ CellRange block_cells(bool in, const int (&j0)[3], int* scratch,
                                                  unsigned (&q)[3]) {
   unsigned* s = reinterpret_cast<unsigned*>(scratch);
-  cells_to_slots(in, j0, s);
+  cells_to_slots<NEAR>(in, j0, s);
   __syncthreads();
   cells_from_slots(s, q);
   return cells_decode(q);

@@ -53,12 +53,13 @@ __device__ inline bool deposit_footprint(int M, double ux, double uy, double uz,
 // particle drops is one unit minus what it keeps (the eight weights sum to exactly one
 // unit).  FP32 plans store the block's total (at most 256 x 2^21 units) in word 3 of
 // hint_out, for the Poisson pass that consumes this deposit to fold into the box's counter,
-// and return 0; FP64 plans store 0 there and return this thread's dropped mass.  SKIP: a wave
-// that drops nothing skips the sums of what it keeps (fewer vector instructions, 1 % of the
-// particle step; in the persistent step, whose few waves wait for one another, the branch costs
-// more: 20.2 ms for 10 steps of one box of 128^3 with it, 19.1 without).  Must be called by all
-// threads of the block.
-template <typename T, bool SKIP = true>
+// and return 0; FP64 plans store 0 there and return this thread's dropped mass.  NEAR: with the
+// shortcuts for the usual case, cells near one another (see cells_to_slots) and no dropped mass.
+// They pay where the deposit is all there is (64 boxes of 64^3: 251 us without, 237 with); behind
+// a force they do not (6 FP64 steps of 64 boxes of 32^3 0.840 ms with, 0.831 without; 10 order-4
+// steps of 64 of 64^3 5.95 and 5.84; the persistent step of one box of 128^3, 10 steps, 20.2 and
+// 19.1).  Must be called by all threads of the block.
+template <typename T, bool NEAR = true>
 __device__ __forceinline__ long long deposit_block(typename MeshFixed<T>::rho_t* __restrict__ rho, int M,
                                           bool active, double ux, double uy, double uz,
                                           typename MeshFixed<T>::window_t* win, int* bounds,
@@ -72,16 +73,23 @@ __device__ __forceinline__ long long deposit_block(typename MeshFixed<T>::rho_t*
   WeightT<T> w[8];
   if (in) mesh_weights<T>(f[0], f[1], f[2], w);
   // which of the two corner planes along each axis are interior nodes
-  const auto inner = [&](int c, int k) { return j0[c] + k >= 1 && j0[c] + k <= n; };
-  // the mass each particle drops; a wave whose corners are all interior, the usual case, drops
-  // none
+  bool low[3], high[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    low[c] = j0[c] >= 1 && j0[c] <= n;
+    high[c] = j0[c] >= 0 && j0[c] <= n - 1;
+  }
+  const auto inner = [&](int c, int k) {
+    return NEAR ? j0[c] + k >= 1 && j0[c] + k <= n : k ? high[c] : low[c];
+  };
+  // the mass each particle drops: none in a wave whose corners are all interior
   constexpr bool kBlockDrop = MeshFixed<T>::bits < 32;
   long long dropped = 0;
-  const bool whole = SKIP && in && (unsigned)(j0[0] - 1) < (unsigned)(n - 1) &&
+  const bool whole = NEAR && in && (unsigned)(j0[0] - 1) < (unsigned)(n - 1) &&
                      (unsigned)(j0[1] - 1) < (unsigned)(n - 1) &&
                      (unsigned)(j0[2] - 1) < (unsigned)(n - 1);
   unsigned d = 0;
-  if (!SKIP || !__all(whole)) {
+  if (!NEAR || !__all(whole)) {
     WeightT<T> kept = 0;
     if (in) {
 #pragma unroll
@@ -109,7 +117,7 @@ __device__ __forceinline__ long long deposit_block(typename MeshFixed<T>::rho_t*
     for (int k = 0; k < kClear; ++k) w4[threadIdx.x + kBlock * k] = make_uint4(0u, 0u, 0u, 0u);
   }
   unsigned q[3];
-  const CellRange cr = block_cells(in, j0, bounds, q);
+  const CellRange cr = block_cells<NEAR>(in, j0, bounds, q);
   if (threadIdx.x == 0) {
     unsigned bd = 0u;
     if constexpr (kBlockDrop) {
@@ -676,6 +684,7 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
     else
       staged = stage_wide_direct<T, NG>(a.phi + t.h_off, M, hc, reinterpret_cast<T*>(win));
   }
+  constexpr bool kNear = MODE != kStep;   // see deposit_block
   const StepScalars sc = a.sc;
   double u[3];
 #pragma unroll
@@ -724,15 +733,15 @@ __device__ __forceinline__ void particles_block(const ParticleArgs<T>& a, const 
   }
   if constexpr (MeshFixed<T>::bits < 32) {
     // FP32: the block's dropped mass travels in its hint (folded by the Poisson pass)
-    deposit_block<T, !PERSISTENT>(a.rho + t.g_off, M, true, u[0], u[1], u[2],
-                                  reinterpret_cast<typename MeshFixed<T>::window_t*>(win), bounds,
-                                  hint);
+    deposit_block<T, kNear>(a.rho + t.g_off, M, true, u[0], u[1], u[2],
+                            reinterpret_cast<typename MeshFixed<T>::window_t*>(win), bounds, hint);
   } else {
     __shared__ unsigned long long block_drop;
     if (threadIdx.x == 0) block_drop = 0ull;
     const long long drop =
-        deposit_block<T>(a.rho + t.g_off, M, true, u[0], u[1], u[2],
-                         reinterpret_cast<typename MeshFixed<T>::window_t*>(win), bounds, hint);
+        deposit_block<T, kNear>(a.rho + t.g_off, M, true, u[0], u[1], u[2],
+                                reinterpret_cast<typename MeshFixed<T>::window_t*>(win), bounds,
+                                hint);
     // one atomic per block on the box's counter, which all blocks of the box share
     if (drop != 0) atomicAdd(&block_drop, (unsigned long long)drop);
     __syncthreads();
