@@ -56,40 +56,45 @@ constexpr int first_pass_waves() {
 // and 276, 128^3 453 and 367; reverse third pass of 80^3 to 128^3 146, 222, 411, 539 and 129,
 // 197, 324, 481.  The third pass of 96^3, whose six tiles leave two of eight waves idle in the
 // products, takes the same time either way (64 boxes 159 and 153, 512 boxes 1046 and 1059).  The
-// pencils of 128^3, whose eight tiles four waves share evenly, are faster with 256 (367 and 393).
+// pencils of 128^3, whose eight tiles four waves share evenly, are faster with 256 where they
+// fill the chip (64 boxes 360 and 392, 8 boxes 55 and 56; one box, a block per CU, 16 and 14).
 // 64 R threads, where no wave is idle, were slower (96^3, 512 boxes: 1522, 1049 and 1244): six or
 // seven waves do not spread evenly over the four SIMDs.
-template <typename T, int R, int PASS>
+template <typename T, int R>
 constexpr int pass_threads() {
-  if (!std::is_same<T, float>::value || R < 5) return kBlock;
-  return PASS == 2 && R == 8 ? kBlock : 512;
+  return std::is_same<T, float>::value && R >= 5 ? 512 : kBlock;
+}
+// of the pencil pass in launches of more than kFewChunks chunks (8 boxes of 128^3 have 2024)
+constexpr int kFewChunks = 2048;
+template <typename T, int R>
+constexpr int many_pencils_threads() {
+  return R == 8 ? kBlock : pass_threads<T, R>();
 }
 
 template <typename T, int R, bool ADJ, int NG>
-__global__ void __launch_bounds__((pass_threads<T, R, 1>()))
+__global__ void __launch_bounds__((pass_threads<T, R>()))
 __attribute__((amdgpu_waves_per_eu(first_pass_waves<T, R, ADJ, NG>())))
 k_poisson_p1(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p1_block<T, R, ADJ, NG, pass_threads<T, R, 1>()>(a, m, L, smem);
+  if (L < m.count) poisson_p1_block<T, R, ADJ, NG, pass_threads<T, R>()>(a, m, L, smem);
 }
 
-template <typename T, int R>
-__global__ void __launch_bounds__((pass_threads<T, R, 2>()))
-__attribute__((amdgpu_waves_per_eu(pass_waves<T, R>())))
+template <typename T, int R, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves<T, R>())))
 k_poisson_p2(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p2_block<T, R, pass_threads<T, R, 2>()>(a, m, L, smem);
+  if (L < m.count) poisson_p2_block<T, R, NT>(a, m, L, smem);
 }
 
 template <typename T, int R, bool ADJ, int NG>
-__global__ void __launch_bounds__((pass_threads<T, R, 3>()))
+__global__ void __launch_bounds__((pass_threads<T, R>()))
 __attribute__((amdgpu_waves_per_eu(pass_waves<T, R, ADJ, NG>())))
 k_poisson_p3(MeshArgs<T> a, BlockMap m) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int L = logical_block(m);
-  if (L < m.count) poisson_p3_block<T, R, ADJ, NG, pass_threads<T, R, 3>()>(a, m, L, smem);
+  if (L < m.count) poisson_p3_block<T, R, ADJ, NG, pass_threads<T, R>()>(a, m, L, smem);
 }
 
 }  // namespace
@@ -132,6 +137,7 @@ hipError_t launch_poisson_R(const MeshArgs<T>& a, const BlockMap& p1, const Bloc
                             const BlockMap& p3, hipStream_t s) {
   const size_t l1 = poisson_lds_bytes<T>(16 * R, 1, NG), l2 = poisson_lds_bytes<T>(16 * R, 2, NG),
                l3 = poisson_lds_bytes<T>(16 * R, 3, NG);
+  constexpr int kNT = pass_threads<T, R>(), kMany = many_pencils_threads<T, R>();
   if (l1 > 65536 || l2 > 65536 || l3 > 65536) {
     // allow more than 64 KiB of dynamic LDS (160 KiB on gfx950): a function attribute of
     // each device, set once per device
@@ -144,7 +150,10 @@ hipError_t launch_poisson_R(const MeshArgs<T>& a, const BlockMap& p1, const Bloc
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_poisson_p1<T, R, ADJ, NG>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)l1);
       if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_poisson_p2<T, R>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_poisson_p2<T, R, kNT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)l2);
+      if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_poisson_p2<T, R, kMany>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)l2);
       if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_poisson_p3<T, R, ADJ, NG>),
@@ -153,15 +162,16 @@ hipError_t launch_poisson_R(const MeshArgs<T>& a, const BlockMap& p1, const Bloc
       done.fetch_or(bit);
     }
   }
+  const dim3 block(kNT);
   if (p1.count > 0)
-    hipLaunchKernelGGL((k_poisson_p1<T, R, ADJ, NG>), dim3(padded_grid(p1)),
-                       dim3(pass_threads<T, R, 1>()), l1, s, a, p1);
-  if (p2.count > 0)
-    hipLaunchKernelGGL((k_poisson_p2<T, R>), dim3(padded_grid(p2)),
-                       dim3(pass_threads<T, R, 2>()), l2, s, a, p2);
+    hipLaunchKernelGGL((k_poisson_p1<T, R, ADJ, NG>), dim3(padded_grid(p1)), block, l1, s, a, p1);
+  if (p2.count > kFewChunks)
+    hipLaunchKernelGGL((k_poisson_p2<T, R, kMany>), dim3(padded_grid(p2)), dim3(kMany), l2, s, a,
+                       p2);
+  else if (p2.count > 0)
+    hipLaunchKernelGGL((k_poisson_p2<T, R, kNT>), dim3(padded_grid(p2)), block, l2, s, a, p2);
   if (p3.count > 0)
-    hipLaunchKernelGGL((k_poisson_p3<T, R, ADJ, NG>), dim3(padded_grid(p3)),
-                       dim3(pass_threads<T, R, 3>()), l3, s, a, p3);
+    hipLaunchKernelGGL((k_poisson_p3<T, R, ADJ, NG>), dim3(padded_grid(p3)), block, l3, s, a, p3);
   return hipGetLastError();
 }
 

@@ -51,3 +51,23 @@ def test_reverse_passes_with_few_cell_changes(buffer):
     assert moved <= 3
     rel = float((grad["fp32"] - grad["fp64"]).norm() / grad["fp64"].norm())
     assert rel < 1e-4 + 2e-3 * moved
+
+
+def test_many_boxes_of_128_as_one_alone():
+    """The pencils of many boxes of 128^3 take another block size than those of a few: the same
+    bits for a box among 64 and by itself."""
+    import torch
+
+    import paper_2003_04925_amd as S
+    sim = S.Simulation(128.0, 32, S.uniform_tiling(32, 4, 60), 2)
+    sim.setup(torch.from_numpy(synthetic.white_noise(32, 11)).cuda())
+    sim.evolve()
+    P, h = 128 ** 3, 131 ** 3
+    want = {k: sim.view(k)[:, 37 * P:38 * P].clone() for k in ("x_res", "p_res")}
+    phi = sim.view("phi")[37 * h:38 * h].clone()
+    for k in ("x_res", "p_res", "phi"):
+        sim.view(k).fill_(-7.0)
+    sim.evolve([37])
+    for k in want:
+        assert torch.equal(sim.view(k)[:, 37 * P:38 * P], want[k]), k
+    assert torch.equal(sim.view("phi")[37 * h:38 * h], phi)
