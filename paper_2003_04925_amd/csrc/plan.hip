@@ -1085,8 +1085,14 @@ void do_evolve(scola_plan* p, const std::vector<int>& tiles, void* ws, hipStream
     // find them captured.  Subsets of a plan with the persistent step get one too: cooperative
     // launches keep a hardware queue of their own, and four more streams then take turns on the
     // others (4 boxes of 32^3, 6 FP32 steps: 0.64 ms on one stream, 0.90 on four; 0.46 on four
-    // without cooperative launches in the process).
-    int S = allow_groups && !p->persistent ? std::min<int>(4, (int)tiles.size()) : 1;
+    // without cooperative launches in the process).  A single step of a few small boxes is over
+    // before the streams have forked and joined (one FP32 step of 3 boxes of 16^3: 82 us on one
+    // stream, 112 on three; but 8 boxes 196 and 200, two steps of 3 boxes 144 and 139, and one
+    // step of 5 boxes of 48^3 176 and 154).
+    int largest = 0;
+    for (int t : tiles) largest = std::max(largest, p->desc[t].M);
+    const bool brief = n == 1 && tiles.size() < 8 && largest <= 32;
+    int S = allow_groups && !p->persistent && !brief ? std::min<int>(4, (int)tiles.size()) : 1;
     const bool own_capture = p->capture_stream && s == p->capture_stream;
     if (S > 1 && !own_capture && capturing(s)) S = 1;
     std::vector<int64_t> load(S, 0);

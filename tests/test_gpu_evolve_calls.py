@@ -191,3 +191,29 @@ def test_subsets_of_a_persistent_plan():
         for k in ("x_res", "p_res"):
             assert torch.equal(a.view(k), b.view(k)), k
     assert b.persistent()["barrier_failures"] == 0
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("Np,buffer", [(16, 4), (32, 8), (32, 16)])
+def test_single_step_subsets(precision, Np, buffer):
+    """One step of fewer than eight boxes of up to 32^3 stays on one stream, others fork: every
+    subset gives the batched run's bits."""
+    import torch
+
+    import paper_2003_04925_amd as S
+    tiles, w = S.uniform_tiling(Np, 2, buffer), _noise(Np, 10)
+    sim = S.Simulation(4.0 * Np, Np, tiles, 1, precision=precision)
+    sim.setup(w)
+    sim.evolve()
+    want = {k: sim.view(k).clone() for k in ("x_res", "p_res")}
+    for subset in ([7], [0, 6], [5, 1, 2], [0, 1, 2, 3, 4, 5, 7]):
+        for k in want:
+            sim.view(k).fill_(-7.0)
+        sim.evolve(subset)
+        for t, (po, M, go, ho) in enumerate(sim.box_slices()):
+            for k in want:
+                got = sim.view(k)[:, po:po + M ** 3]
+                if t in subset:
+                    assert torch.equal(got, want[k][:, po:po + M ** 3]), (t, k)
+                else:
+                    assert bool((got == -7.0).all()), (t, k)
