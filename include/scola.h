@@ -331,7 +331,7 @@ scola_status scola_plan_set_schedule(scola_plan* plan, const scola_class_schedul
  * With the per-tile schedule the tiles go out over up to four streams (`stream` and plan-owned
  * ones that fork from and join back to it), and a call whose `stream` the caller is itself
  * capturing enqueues its launches on that stream alone.  It is recorded only where the evolution
- * takes at most 512 launches, 1 + 4 n_steps a tile (5 + 4 n_steps with cfg.want_momenta); larger
+ * takes at most 8192 launches, 1 + 4 n_steps a tile (5 + 4 n_steps with cfg.want_momenta); larger
  * ones, which a graph would slow down, always run eagerly. */
 scola_status scola_plan_set_graph(scola_plan* plan, int32_t enable);
 

@@ -1298,15 +1298,15 @@ int64_t per_tile_launches(const scola_plan* p) {
   return (int64_t)p->desc.size() * (1 + n + last + 3 * (n + last));
 }
 
-// The per-tile schedule is recorded up to this many launches.  A graph of four branches costs
-// the runtime more per node than the launches themselves on four streams, which run while the
-// host goes on; what it saves is the host's part of a short call.  Recorded and eager, ms per
-// call in a row and (waited for): 1 box of 16^3, 97 launches, 0.47 and 0.53 (0.48, 0.54);
-// 8 of 32^3, 136, 0.45 and 0.51 (0.53, 0.56); 8 of 48^3 in FP64, 264, 1.01 and 1.01 (1.40,
-// 1.27); 8 of 32^3 in FP64, 776, 1.93 and 2.01 (2.95, 2.52); 64 of 32^3 in FP64, 576, 1.90 and
-// 1.80 (2.38, 1.85), 1088, 3.77 and 3.27 (4.69, 3.29); 64 of 64^3, 5120, 20.3 and 18.6 (27.2,
-// 19.4); 512 of 16^3, 61440, 314 and 227, after a recording of 390 ms.
-constexpr int64_t kPerTileGraphLaunches = 512;
+// The per-tile schedule is recorded up to this many launches.  A graph saves the host's part of
+// them (3 to 4 us each over four streams), but its own cost per node grows with the graph and is
+// paid before the GPU can start.  FP64 runs in a row, recorded and eager, ms: 8 boxes of 48^3, 520
+// launches, 2.00 and 2.48, 776, 2.87 and 3.63; 64 of 48^3, 2112, 7.73 and 9.82, 6208, 27.1 and
+// 28.6; 64 of 32^3, 6208, 22.2 and 23.2; 512 of 16^3, 8704, 30.8 and 30.7, 14848, 61.8 and 52.5,
+// 49664, 288 and 181; 512 of 32^3, 20992, 130 and 77.  A call that is waited for gains less: 2.8
+// and 2.5 ms at 520, 27 and 24 at 6208.  The recording, in the second call, takes about as long
+// as the call.
+constexpr int64_t kPerTileGraphLaunches = 8192;
 
 void drop_graph(scola_plan* p) {
   if (p->evolve_exec) hipGraphExecDestroy(p->evolve_exec);

@@ -77,17 +77,17 @@ def test_eager_call_while_the_caller_records_another(graph):
         assert torch.equal(pos, ref)
 
 
-@pytest.mark.parametrize("Np,per_side,steps,momenta,recorded", [
-    (32, 2, 4, False, True), (32, 2, 15, False, True), (32, 2, 16, False, False),
-    (32, 2, 14, True, True), (32, 2, 15, True, False), (64, 4, 4, False, False)])
-def test_per_tile_recording_is_bounded(Np, per_side, steps, momenta, recorded):
-    """At most 512 launches of the per-tile schedule become a graph (8 tiles: 15 steps, 14 with
+@pytest.mark.parametrize("Np,per_side,buffer,steps,momenta,recorded", [
+    (32, 2, 8, 4, False, True), (64, 8, 4, 3, False, True), (64, 8, 4, 4, False, False),
+    (64, 8, 4, 2, True, True), (64, 8, 4, 3, True, False)])
+def test_per_tile_recording_is_bounded(Np, per_side, buffer, steps, momenta, recorded):
+    """At most 8192 launches of the per-tile schedule become a graph (512 tiles: 3 steps, 2 with
     momenta); plans beyond, which a graph slows down, launch their kernels on every call."""
     import torch
     from torch.profiler import ProfilerActivity, profile
 
     import paper_2003_04925_amd as S
-    tiles, w = S.uniform_tiling(Np, per_side, 8), _noise(Np, 5)
+    tiles, w = S.uniform_tiling(Np, per_side, buffer), _noise(Np, 5)
     ref = S.Simulation(4.0 * Np, Np, tiles, steps, want_momenta=momenta).forward(w)["pos"]
     sim = S.Simulation(4.0 * Np, Np, tiles, steps, want_momenta=momenta, schedule="per_tile")
     sim.setup(w)
