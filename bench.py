@@ -211,8 +211,8 @@ def cpu_baseline():
 
 
 def adjoint_timing(torch, S, synthetic, name="c4", reps=3):
-    """Forward with checkpoints (every 5 steps) and the reverse pass (segment recomputation
-    + adjoint steps + FP64 set-up adjoint) of a density loss, HIP-event timed on the current
+    """Forward with checkpoints (every 5 steps) and the reverse pass (recomputation of every
+    segment but the last + adjoint steps + FP64 set-up adjoint) of a density loss, HIP-event timed on the current
     stream: c4 (the c2 boxes, 20 FP32 steps) or c5 (512 boxes of 96^3, 30 FP32 steps)."""
     wl = synthetic.WORKLOADS[name]
     sim = S.Simulation(wl.L, wl.Np, S.uniform_tiling(wl.Np, wl.tiles_per_side, wl.buffer),
@@ -247,8 +247,8 @@ def adjoint_timing(torch, S, synthetic, name="c4", reps=3):
             "forward_ms": f, "backward_ms": g, "backward_over_forward": g / f,
             "workspace_GB": ws_gb, "launch_schedule": {str(k): v for k, v in sched.items()},
             "concurrent_box_groups": groups,
-            "note": "backward = segment recomputation (one forward's worth of steps) + adjoint "
-                    "steps + FP64 set-up adjoint"}
+            "note": "backward = recomputation of every segment but the last + adjoint steps + "
+                    "FP64 set-up adjoint"}
 
 
 def workload_rate(torch, S, synthetic, name, steps=3, warmup=2):

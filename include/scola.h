@@ -241,10 +241,10 @@ scola_status scola_forward_noalloc(scola_plan* plan, const double* d_white_noise
  * (R [N_out^3], device), writes d loss / d white noise (double [N_lpt^3], device).  Needs a
  * plan with checkpoint_every > 0 and a preceding scola_forward over all tiles on the same
  * workspace (else SCOLA_ESTATE).  Segments of checkpoint_every steps are recomputed from
- * the checkpoints (the last one is there from the forward), then reversed step by step: transpose of the drift and kick, of the
- * gradient-then-CiC-interpolation chain (one scalar scatter per particle onto the padded
- * nodes), the same Dirichlet DST solve (the FDA-2 Dirichlet Laplacian is symmetric) and of
- * the deposit; finally the FP64 transposes of Phi_BC^0, Psi = D phi, the second-order
+ * the checkpoints (the last one is there from the forward), then reversed step by step:
+ * transpose of the drift and kick, of the gradient-then-CiC-interpolation chain (one scalar
+ * scatter per particle onto the padded nodes), the same Dirichlet DST solve (the FDA-2
+ * Dirichlet Laplacian is symmetric) and of the deposit; finally the FP64 transposes of Phi_BC^0, Psi = D phi, the second-order
  * source and the initial-condition filter.
  * The particle state left in the workspace afterwards is that of the first segment;
  * run scola_evolve again before scola_output. */
@@ -297,9 +297,9 @@ scola_status scola_evolve_overrides(scola_plan* plan, const void* d_delta, const
  * deposits, and synchronises the stream (call it before scola_evolve, never inside a timed
  * or captured region).  Its timed evolutions leave x_res and p_res at the end of an
  * evolution; scola_evolve starts from L- whatever they hold, so runs after tuning are
- * bitwise those without it.  scola_plan_schedule copies the schedule of every class into out (capacity
- * entries at least; out may be NULL to query *n_classes).  scola_plan_set_schedule sets it
- * (same classes, same order). */
+ * bitwise those without it.  scola_plan_schedule copies the schedule of every class into out
+ * (capacity entries at least; out may be NULL to query *n_classes).  scola_plan_set_schedule
+ * sets it (same classes, same order). */
 typedef struct {
   int32_t M;
   int32_t waves_per_simd;

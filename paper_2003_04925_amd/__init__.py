@@ -349,7 +349,8 @@ class Simulation:
         return out
 
     def set_graph(self, enable):
-        """Replay the batched evolution as a captured hipGraph (default) or run it eagerly."""
+        """Replay the evolution as a captured hipGraph (default; see scola_plan_set_graph) or run
+        it eagerly."""
         _lib.check(_lib.lib().scola_plan_set_graph(self._plan, 1 if enable else 0))
 
     def set_persistent(self, enable):
