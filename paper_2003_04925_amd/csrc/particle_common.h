@@ -17,8 +17,8 @@ namespace {
 // particle step and the extraction of Psi stream 18 and 6 arrays from memory, and eight XCDs
 // far apart in each of them reach less of its bandwidth than XCDs that advance together: runs
 // of four bricks, neighbours along z with their shared window nodes, are faster than ranges and
-// than single blocks (evolution of 64 boxes of 64^3: 8.44 against 8.65 and 8.66 ms, runs of 8
-// 8.54, of 2 8.60; 64 boxes of 96^3: 30.45 against 32.26 and 30.53, runs of 8 30.61).
+// than single blocks (20 steps of 64 boxes of 64^3: 8.45 against 8.60 and 8.58 ms, and runs of 8
+// or of 2 lie between; 10 steps of 64 boxes of 96^3: 15.3 against 16.2 and 15.4).
 __device__ inline int logical_block(const BlockMap& m) {
   const int b = blockIdx.x;
   if (m.xcd_remap == kXcdNone) return b;
